@@ -12,32 +12,43 @@ constexpr size_t kMaxLds = 160 * 1024;
 
 int round_rp(int R) { return (R + 31) / 32 * 32; }
 
+size_t esize(carve_dtype_t dt) { return dt == CARVE_BF16 ? 2 : 4; }
+
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// 16-token tiles of the backward's WY blocks (1, 2 or 4, dividing the chunk):
+// the largest whose LDS layout fits
+int pick_nb(const carve_dims_t* d) {
+  const int RP = round_rp(d->R);
+  for (int nb = 4; nb >= 1; nb /= 2) {
+    if (16 * nb > d->L || d->L % (16 * nb)) continue;
+    if (bwd_lds_bytes(d->dtype, d->Dk, nb, RP) <= kMaxLds) return nb;
+  }
+  return 0;
+}
 
 // backward workspace: d[Ub; Uw] partials per (b,h, chunk split) | dVb, dVw
 // partials per (b,h, token split) | chunk records of the recompute | ready
 // flags and ticket counter of the fused recompute + adjoint launch
 struct BwdWs {
-  size_t part, partV, rec, sync, partG, total;
+  size_t part, partV, rec, sync, partG, opnd, total;
 };
 
 BwdWs bwd_workspace_layout(const carve_dims_t* d) {
   BwdWs l{};
   const size_t nbh = (size_t)d->B * d->H;
-  const size_t es = d->dtype == CARVE_BF16 ? 2 : 4;
   const size_t nch = (size_t)(d->T / d->L);
   size_t off = 0;
   l.part = off;  off += align256(nbh * kUSplit * part_floats(d->R, d->Dk) * 4);
   l.partV = off; off += align256(nbh * kVSplit * part_floats(d->R, d->Dk) * 4);
   // records of the full layer (2RP fold rows); the scalar-write records are smaller
-  l.rec = off;   off += align256(nbh * nch * chunk_rec(es, d->Dk, d->L, 2 * round_rp(d->R)).total);
+  l.rec = off;   off += align256(nbh * nch * chunk_rec_bytes(d->dtype, d->Dk, d->L, 2 * round_rp(d->R), pick_nb(d)));
   l.sync = off;  off += align256(sync_ints(nbh, nch) * sizeof(int));
   l.partG = off; off += align256(nbh * 2 * (size_t)d->Dk * 4);   // dA, dtau partials (gated)
+  l.opnd = off;  off += align256(nbh * adj_opnd_bytes(d->Dk, 2 * round_rp(d->R), esize(d->dtype)));
   l.total = off;
   return l;
 }
-
-size_t esize(carve_dtype_t dt) { return dt == CARVE_BF16 ? 2 : 4; }
 
 int check_dims(const carve_dims_t* d) {
   if (!d) return CARVE_ERR_NULL;
@@ -54,22 +65,6 @@ int check_dims(const carve_dims_t* d) {
   if ((long long)d->B * d->H > (1LL << 30)) return CARVE_ERR_UNSUPPORTED;
   if ((long long)d->T * d->H * (d->Dk > d->Dv ? d->Dk : d->Dv) >= (1LL << 31)) return CARVE_ERR_UNSUPPORTED;
   return CARVE_OK;
-}
-
-// largest recompute sub-chunk (<= 32 tokens, dividing L) for which the LDS
-// layout of the fused recompute + adjoint launch fits.  32-token sub-chunks
-// keep the recompute's registers within the file (64-token ones spill 64 of
-// them) and recompute fastest: measured against 64 and 16 tokens, the fused
-// launch took 1.32 against 1.49 and 1.41 ms at B = 8, H = 16, T = 2048 (where
-// the recompute bounds it) and 1.885 against 1.90 and 1.884 ms at the
-// 1.3B-scale T = 4096 layer (where the adjoint does)
-int pick_lw(const carve_dims_t* d) {
-  const int RP = round_rp(d->R);
-  for (int lw = 32; lw >= 16; lw /= 2) {
-    if (lw > d->L || d->L % lw) continue;
-    if (bwd_lds_bytes(d->dtype, d->Dk, lw, RP) <= kMaxLds) return lw;
-  }
-  return 0;
 }
 
 // compute units of the current device (the fused backward sizes its grid by it)
@@ -173,7 +168,7 @@ int carve_bwd_wait_status(const carve_dims_t* d, const void* workspace, hipStrea
   if (!d || !workspace || !timed_out) return CARVE_ERR_NULL;
   int st = check_dims(d);
   if (st) return st;
-  if (!pick_lw(d)) return CARVE_ERR_UNSUPPORTED;
+  if (!pick_nb(d)) return CARVE_ERR_UNSUPPORTED;
   const BwdWs wl = bwd_workspace_layout(d);
   const int* word = reinterpret_cast<const int*>(reinterpret_cast<const char*>(workspace) + wl.sync) +
                     sync_timeout_word((size_t)d->B * d->H, (size_t)(d->T / d->L));
@@ -187,7 +182,7 @@ int carve_bwd_wait_status(const carve_dims_t* d, const void* workspace, hipStrea
 size_t carve_workspace_size(const carve_dims_t* d, int for_backward) {
   if (check_dims(d) != CARVE_OK) return 0;
   if (!for_backward) return 0;
-  if (!pick_lw(d)) return 0;
+  if (!pick_nb(d)) return 0;
   return bwd_workspace_layout(d).total;
 }
 
@@ -296,8 +291,8 @@ int bwd_impl(const carve_dims_t* d, const void* q, const void* k, const void* v,
                         {dwx, nwx}, {dUb, RDv}, {dUw, RDv}, {dVb, RDv},
                         {dVw, RDv}, {dS0, nst * 4}};
   if (any_overlap(outs, 15, ins, 18)) return CARVE_ERR_UNSUPPORTED;
-  const int lw = pick_lw(d);
-  if (!lw) return CARVE_ERR_UNSUPPORTED;
+  const int nb = pick_nb(d);
+  if (!nb) return CARVE_ERR_UNSUPPORTED;
   int cus = 0;
   st = device_cus(&cus);
   if (st) return st;
@@ -323,14 +318,15 @@ int bwd_impl(const carve_dims_t* d, const void* q, const void* k, const void* v,
   a.partV = reinterpret_cast<float*>(wsb + wl.partV);
   a.partG = reinterpret_cast<float*>(wsb + wl.partG);
   a.rec = wsb + wl.rec;
-  a.B = d->B; a.T = d->T; a.H = d->H; a.R = d->R; a.RP = RP; a.L = d->L;
+  a.opnd = wsb + wl.opnd;
+  a.B = d->B; a.T = d->T; a.H = d->H; a.R = d->R; a.RP = RP; a.L = d->L; a.NB = nb;
   a.wait_limit = g_wait_limit;
   int* sync = reinterpret_cast<int*>(wsb + wl.sync);
   prof_mark(stream);
   st = launch_sync_clear(sync, sync_ints((size_t)d->B * d->H, (size_t)(d->T / d->L)), stream);
   if (st) return st;
   prof_mark(stream);
-  st = launch_bwd_fused(f, a, sync, cus, d->dtype, d->Dk, lw, variant_of(dc, sw, act), stream);
+  st = launch_bwd_fused(f, a, sync, cus, d->dtype, d->Dk, nb, variant_of(dc, sw, act), stream);
   if (st) return st;
   prof_mark(stream);
   // 3. in one launch: d[Ub; Uw] from the per-chunk dF, dVb, dVw from dbx, dwx

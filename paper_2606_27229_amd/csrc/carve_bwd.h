@@ -6,59 +6,61 @@
 //   1. carve_sync_clear_kernel: zeroes the chunk ready flags and the ticket
 //      counter of step 2 (a fill kernel, so the sequence may be graph-captured);
 //   2. carve_bwd_fused_kernel: two kinds of workgroup in one grid.
-//      Recompute workgroups (rec_chunk, carve_rec.h) recompute chunks
+//      Recompute workgroups (rec_run, carve_rec.h) recompute chunks
 //      independently from S_chunks, latest chunks first, and write a chunk
-//      record each (F, tau, T and P of every 16-token block, the block
-//      retentions and the block start states), then raise that chunk's ready
-//      flag.  Adjoint workgroups (bwd_adjoint below), one per (batch, head),
-//      walk the chunks and their 16-token blocks in reverse, carry the state
-//      gradient and wait for a chunk's flag before reading its record, so the
-//      recompute runs on the compute units the adjoint leaves idle, ahead of it;
+//      record each, then raise that chunk's ready flag.  Adjoint workgroups
+//      (Adjoint below), one per (batch, head), walk the chunks and their WY
+//      blocks in reverse, carry the state gradient and wait for a chunk's flag
+//      before reading its record, so the recompute runs on the compute units
+//      the adjoint leaves idle, ahead of it;
 //   3. carve_bwd_param_kernel: d[Ub; Uw] from the per-chunk dF (parked in the
 //      chunk records by step 2) and the chunk start states, split over
 //      chunks, and dVb, dVw from dbx, dwx and tau, split over tokens;
 //   4. carve_param_reduce_kernel: fixed-order sums of the parameter partials,
 //      so reruns are bitwise identical.
 //
-// Adjoint of one 16-token block (wave w owns value tile w and key tile w; the
-// state gradient dS lives in registers as dS^T tiles, rows = key index j,
-// columns = the wave's 16 value rows).  The block is evaluated relative to the
-// per-key-channel reference rho = lam_15 / 2, the middle of its log-retention
-// range: with Sr = S diag(e^{rho}) the block start state as the chunk record
-// holds it, gam = e^{lam_15 - rho} (= e^{rho}), dS' the gradient of the block
-// end state (Sr + u^T Ki) diag(gam), and lam, Kt, Qt, Ki (relative to rho), A,
-// P, T, R, u as in the recompute:
-//   dM   = dS' diag(gam)
+// Adjoint of one WY block of NB 16-token tiles (wave w owns value tile w and
+// key tile w; the state gradient dS lives in registers as dS^T tiles, rows = key
+// index j, columns = the wave's 16 value rows).  The block is evaluated
+// relative to the per-key-channel reference rho = lam_end / 2, the middle of
+// its log-retention range.  With S' = S diag(e^{rho}) the scaled block start
+// state, gam = e^{rho}, dS_end the gradient of the block end state (S' + u^T Ki)
+// diag(gam), and lam, Kh = beta Kt, Qt, Ki (relative to rho), A, P, T, R, u as in
+// the recompute:
+//   dM   = dS_end diag(gam)
 //   du   = Ki dM^T + P^T dO             (du_s = dM Ki_s + sum_t P_ts dO_t)
-//   dR   = T^T du,  dX = -beta dR,  d(w v) = beta dR
-//   dS   = (dM + dO^T Qt + dX^T Kt) diag(e^{rho})   (state gradient at the block start)
-//   dKt  = dX Sr + beta dA Ki            dA = -dR u^T (s < t)
-//   dQt  = dO Sr + dP Ki                 dP = dO u^T  (s <= t)
-//   dKi  = diag(gam) dS'^T u + (beta dA)^T Kt + dP^T Qt
-//   dbeta = rowsum(dR (w v - S Kt)) + rowsum(dA A0)    (A0 = Kt Ki^T)
-//   dgam gam = gam (diag(dS'^T Sr) + sum_s Ki_s (dS'^T u_s))
-//   dlam_t = dQt_t Qt_t - dKi_t Ki_t + dKt_{t+1} Kt_{t+1} + [t = 15] dgam gam
+//   dR   = (I + A)^{-T} du              (blocked back substitution with T_ii, A_ij)
+//   dS   = (dM + dO^T Qt - dR^T Kh) diag(e^{rho})   (gradient at the block start)
+//   y    = -dR S' + dA Ki               dA = -dR u^T (s < t)
+//   dQt  = dO S' + dP Ki                dP = dO u^T  (s <= t)
+//   dKi  = dM^T u + dA^T Kh + dP^T Qt
+//   dKt  = beta y,   d(beta w v) = dR
+//   dbeta = rowsum(dR (w v)) + rowsum(Kt y)
+//   dgam gam = diag(dM^T S') + sum_s Ki_s (dM^T u_s)
+//   dlam_t = dQt_t Qt_t - dKi_t Ki_t + y_{t+1} Kh_{t+1} + [t = end] dgam gam
 //   dl = suffix sums of dlam;  dg = dl;  dz_b = -dl b
 //   dk = dKt e^{lam_{t-1} - rho} + dKi e^{rho - lam_t},  dq = dQt e^{lam_t - rho} + dY F
 // rho is a constant of the block (the block's result does not depend on it), so
-// the gradients through lam are those above with rho held fixed.  No factor
-// exceeds e^{|lam_15| / 2}.  This kernel takes rho from its own prefix sums; the
-// recompute scaled the record's Sr by its own, equal up to the rounding of the
-// two evaluations of the same sums (a relative difference of order 1e-6 in the
-// factors, far below the token dtype's rounding).
+// the gradients through lam are those above with rho held fixed.  The factors
+// Kh, Qt, Ki that multiply their gradients in dlam and dgam are the token-dtype
+// values of the operand tiles, exactly as the products consumed them: the pair
+// terms of A and P (and the u^T Ki term of the state carry) enter dlam twice
+// with opposite signs and cancel in the suffix sums only then (bf16: with one
+// factor unrounded, about 1 % of dl is left instead of 0.2 %).
 //   dv = d(wv) w,  dz_w = d(wv) v w (1 - w)
 //   dtau = [dz_b Vb, dz_w Vw],  dY = dtau (1 - tau^2),  dF += dY^T q
 // and at the chunk start the folded read-out closes the chain ("glue"):
 //   dS += [Ub; Uw]^T dF,   d[Ub; Uw] += dF S_hat^T.
+// A block that the recompute evaluated tile by tile (carve_rec.h) is walked as
+// NB blocks of one tile.
 // With the scalar write gate (kVarScalarW; w_t = sigmoid(wx_t) on every value
 // channel, no write-side content) the fold is Ub S_hat alone, there is no
 // dtau_w, and the gradient of the token's write logit is the sum over the
 // value channels: dwx_t = sum_v d(wv)_tv v_tv w_t (1 - w_t).
-// With the input activations (kVarAct) the token tiles of q, k, v are staged
-// raw; the inverse L2 norms of the block's SiLU(k), SiLU(q) rows are summed
-// while staging, the quads are activated when read, and dv is taken through
-// SiLU' here.  dq and dk leave this kernel as gradients of the activated q, k;
-// carve_act_bwd_kernel takes them through the L2 normalisation and SiLU.
+// With the input activations (kVarAct) the records hold the activated q, k, v,
+// and dv is taken through SiLU' here.  dq and dk leave this kernel as gradients
+// of the activated q, k; carve_act_bwd_kernel takes them through the L2
+// normalisation and SiLU.
 #pragma once
 #include "carve_rec.h"
 
@@ -66,890 +68,794 @@ namespace carve {
 
 // Bound of the ready-flag wait: 2^20 polls (each a few device-scope
 // loads and a short sleep; about a second in all).  A chunk is recomputed in
-// tens of microseconds by a workgroup that never waits, so the bound is not
-// reached in a correct launch; if it is, the waiting wave poisons its state
-// gradient with NaN (every gradient of earlier tokens then comes out NaN),
-// sets the wait-timeout word of the synchronisation area and waits no more.
-// The bound is a kernel argument (BwdArgs::wait_limit, kReadySpinLimit unless
-// a test sets it) so that tests can make the wait give up from the host while
-// every kernel still runs to completion.
-// chunks whose flags one wait inspects (need, need - 1, ...)
-constexpr int kReadyWindow = 8;
+// tens of microseconds by a workgroup that never waits for long, so the bound
+// is not reached in a correct launch; if it is, every wave poisons its state
+// gradient with NaN (every gradient of earlier tokens then comes out NaN), the
+// wait-timeout word of the synchronisation area is set and the workgroup waits
+// no more.  The bound is a kernel argument (BwdArgs::wait_limit,
+// kReadySpinLimit unless a test sets it) so that tests can make the wait give
+// up from the host while every kernel still runs to completion.
 // how many chunks ahead of the adjoint the recompute works, and the bound of
 // its wait for the adjoint's position (2^16 polls of a few hundred cycles:
 // milliseconds, far beyond a chunk's time)
 constexpr int kRecomputeLead = 4;
 constexpr int kLeadSpinLimit = 1 << 16;
 
-// Wait until chunk `need`'s flag is raised (flags are raised with release
-// stores at agent scope) and return the lowest chunk lo such that the flags of
-// chunks lo .. need, within a window of kReadyWindow chunks, were all seen
-// raised; one acquire fence then covers all of them, so a wave pays for one
-// cache invalidation per window instead of one per chunk.  Every lane reads
-// every flag itself.  Returns need + 1 if the bound (`limit` polls) ran out.
-__device__ __forceinline__ int acquire_ready(const int* rdy, const int need, const int limit) {
-  for (int n = 0; n < limit; ++n) {
-    // unconditional loads from clamped indices (issued back to back), masked after
-    int f[kReadyWindow];
-#pragma unroll
-    for (int i = 0; i < kReadyWindow; ++i)
-      f[i] = __hip_atomic_load(rdy + (need - i >= 0 ? need - i : 0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-    for (int i = 1; i < kReadyWindow; ++i)
-      if (need - i < 0) f[i] = 0;
-    if (f[0] != 0) {
-      int lo = need;
-#pragma unroll
-      for (int i = 1; i < kReadyWindow; ++i) {
-        if (f[i] == 0) break;
-        lo = need - i;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      return lo;
-    }
-    __builtin_amdgcn_s_sleep(2);
-  }
-  return need + 1;
-}
-
 // Compiler-only fence: keeps the LDS loads of one loop iteration from being
 // hoisted above the previous one (bounds the number of live operand registers).
 #define CARVE_SEQ() asm volatile("" ::: "memory")
 
-// Adjoint of (batch, head) bh.  ready[bh * nch + ch] is raised when chunk ch's
-// record is complete; smem is the workgroup's dynamic LDS (BwdLds layout).
-// GATED: g is formed from its staged raw logit f (Eq. decay_gate); the kernel
-// writes df = dg (-exp(A)) sigmoid(f + tau_f) instead of dg and sums dA = dg g
-// and dtau = df over its tokens (per lane in registers, reduced once at the
-// end) into a per-(batch, head) partial.
-template <typename T, int D, int RP, int VAR>
-__device__ __forceinline__ void bwd_adjoint(const BwdArgs& a, const int bh, char* smem, const int* ready,
-                                            int* timeout_word, int* pos) {
+// Adjoint of one (batch, head).  GATED: the kernel writes df = dg (-exp(A))
+// sigmoid(f + tau_f) instead of dg and sums dA = dg g and dtau = df over its
+// tokens (per lane in registers, reduced once at the end) into a
+// per-(batch, head) partial.
+//
+// The steps of a block are separated by one workgroup barrier each: value side
+// (B1), products over the value axis (B2), pair terms and gate gradients (B3),
+// dtau (B4), dF / dq and, at a chunk start, the glue (B5).  What a block reads
+// from its record reaches the LDS through registers loaded one or two steps
+// before their region is free (tile images: linear 16-byte copies), so the
+// steps use only LDS, registers and the matrix cores.
+template <typename T, int D, int RP, int VAR, int NBK>
+struct Adjoint {
   typedef Quad<T> Qd;
   typedef typename Qd::q quad;
-  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-  constexpr bool GATED = (VAR & kVarGated) != 0;
-  constexpr bool SW = (VAR & kVarScalarW) != 0;
-  constexpr bool ACT = (VAR & kVarAct) != 0;
-  constexpr int NT = bwd_threads(D);
-  constexpr int NW = NT / 64;
-  constexpr int NJT = D / 16;
-  constexpr int R2 = fold_rows(RP, VAR);
-  constexpr int NRT = R2 / 16;
-  constexpr int NRB = RP / 16;
-  constexpr int PAD = 16 / sizeof(T);
-  constexpr int LDD = D + PAD, LDR = R2 + PAD, LDB = 16 + PAD;
-  // bank-conflict-free layouts (QS): Kt, Qt, Ki, VbT, VwT rows of LDK and the
-  // exchange tiles rows of LDX with the quad swizzle (qx), S and dS' rows of
-  // LDSX (SXH, bf16 d = 128: unpadded with hswz128)
-  constexpr bool QS = bwd_qswz<T, VAR>(), SXH = bwd_sx_hswz<T, D, VAR>();
-  constexpr int LDK = bwd_ldk<T, D, VAR>(), LDX = bwd_ldx<T, VAR>(), LDSX = bwd_ldsx<T, D, VAR>();
-  constexpr int VEC = 16 / sizeof(T);
-  static_assert(NW == NJT, "one wave per 16-wide tile");
-
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int g = lane >> 4, c = lane & 15;
-  // the quad-swizzle term of row r, and the transposing operand read, of the
-  // tiles laid out with QS
-#define CARVE_QX(R_) (QS ? qswz<T>(R_) : 0)
-#define CARVE_LDTR(B_, LD_, R0_, C0_) (QS ? Qd::ld_tr_sw(B_, LD_, R0_, C0_, g, c) : Qd::ld_tr(B_, LD_, R0_, C0_, g, c))
-  const int H = a.H, Tn = a.T, L = a.L, R = a.R;
-  const int b = bh / H, h = bh % H;
-  const int nch = Tn / L, nbc = L / 16;
-
-  constexpr BwdLds lay = bwd_lds<T, D, RP, VAR>();
-  constexpr int NS = bwd_stage_tiles(SW);             // staged token tiles per block
-  // the key-side factors of a block (E and the erase gate) come from the
-  // chunk record, staged in place of g and bx; GATED kernels recompute them
-  // from f, bx and tau
-  constexpr bool KREC = !GATED;
-  T* sF = reinterpret_cast<T*>(smem + lay.F);        // [R2][LDD]    F of the chunk
-  T* sVbT = reinterpret_cast<T*>(smem + lay.VbT);    // [RP][LDK]    Vb^T (quad-swizzled)
-  T* sVwT = reinterpret_cast<T*>(smem + lay.VwT);    // [RP][LDK]    Vw^T (not SW; quad-swizzled)
-  T* sTau = reinterpret_cast<T*>(smem + lay.Tau);    // [16][LDR]    tau of the block
-  T* sTm = reinterpret_cast<T*>(smem + lay.Tm);      // [16][LDB]    T of the block
-  T* sP = reinterpret_cast<T*>(smem + lay.P);        // [16][LDB]    P of the block
-  float* sGam = reinterpret_cast<float*>(smem + lay.Gam);      // [D] gam = e^{rho} of the block
-  float* sBeta = reinterpret_cast<float*>(smem + lay.Beta);    // [16] beta, then [16] sigmoid(wx) (SW)
-  float* sDbeta = reinterpret_cast<float*>(smem + lay.Dbeta);  // [NW + 1][16]
-  float* sDwx = reinterpret_cast<float*>(smem + lay.Dwx);      // [NW][16] (SW)
-  float* sInv = reinterpret_cast<float*>(smem + lay.Inv);      // [2][16] 1/|SiLU(k)|, 1/|SiLU(q)| (ACT)
-  T* sKt = reinterpret_cast<T*>(smem + lay.Kt);      // [16][LDK]    (quad-swizzled)
-  T* sQt = reinterpret_cast<T*>(smem + lay.Qt);      // [16][LDK]
-  T* sKi = reinterpret_cast<T*>(smem + lay.Ki);      // [16][LDK]
-  T* sSx = reinterpret_cast<T*>(smem + lay.Sx);      // [D][LDSX]    S[v][j] (block start)
-  T* sdSx = reinterpret_cast<T*>(smem + lay.dSx);    // [D][LDSX]    dS'[v][j]; glue: dF at (j, r)
-  T* sdOT = reinterpret_cast<T*>(smem + lay.dOT);    // [D][LDX]     [value][token] exchange (quad-swizzled)
-  T* suT = reinterpret_cast<T*>(smem + lay.uT);
-  T* sdRT = reinterpret_cast<T*>(smem + lay.dRT);
-  T* sdzwT = reinterpret_cast<T*>(smem + lay.dzwT);
-  T* sdzb = reinterpret_cast<T*>(smem + lay.dzb);    // [16][LDD]    dz_b[t][j]
-  T* sdY = reinterpret_cast<T*>(smem + lay.dY);      // [16][LDR]    dY[t][r]
-  T* sStg = reinterpret_cast<T*>(smem + lay.Stage);  // [NS][16][D]  token tiles, swizzled
-  float* sGs = reinterpret_cast<float*>(smem + lay.Stage + lds_round(NS * 16 * D * sizeof(T)));  // [16][D] g
-
-  const size_t bh0 = ((size_t)b * Tn * H + h) * D;
-  const size_t bh1 = (size_t)b * Tn * H + h;
-  const int rs = H * D;
-  const T* __restrict__ q = reinterpret_cast<const T*>(a.q) + bh0;
-  const T* __restrict__ k = reinterpret_cast<const T*>(a.k) + bh0;
-  const T* __restrict__ v = reinterpret_cast<const T*>(a.v) + bh0;
-  const T* __restrict__ bx = reinterpret_cast<const T*>(a.bx) + bh0;
-  const T* __restrict__ wx = reinterpret_cast<const T*>(a.wx) + (SW ? bh1 : bh0);
-  const T* __restrict__ beta = reinterpret_cast<const T*>(a.beta) + bh1;
-  const T* __restrict__ dO = reinterpret_cast<const T*>(a.dO) + bh0;
-  const float* __restrict__ gl = GATED ? nullptr : a.g + bh0;
-  const T* __restrict__ fl = GATED ? reinterpret_cast<const T*>(a.f) + bh0 : nullptr;
-  T* __restrict__ dq = reinterpret_cast<T*>(a.dq) + bh0;
-  T* __restrict__ dk = reinterpret_cast<T*>(a.dk) + bh0;
-  T* __restrict__ dv = reinterpret_cast<T*>(a.dv) + bh0;
-  T* __restrict__ dbx = reinterpret_cast<T*>(a.dbx) + bh0;
-  T* __restrict__ dwx = reinterpret_cast<T*>(a.dwx) + (SW ? bh1 : bh0);
-  T* __restrict__ dbeta = reinterpret_cast<T*>(a.dbeta) + bh1;
-  float* __restrict__ dgo = GATED ? nullptr : a.dg + bh0;
-  T* __restrict__ dfo = GATED ? reinterpret_cast<T*>(a.df) + bh0 : nullptr;
-  float* sGate = reinterpret_cast<float*>(smem + lay.Gate);   // [2][D] -exp(A), tau_f (GATED)
-  T* sFs = reinterpret_cast<T*>(sGs);                          // [16][D] staged f (GATED)
-  const ChunkRec cr = chunk_rec(sizeof(T), D, L, R2);
-  const char* recb = reinterpret_cast<const char*>(a.rec) + (size_t)bh * nch * cr.total;
-
-  // ---- shared parameters ------------------------------------------------------
-  for (int x = tid; x < RP * D; x += NT) {
-    const int rr = x / D, j = x % D;
-    sVbT[rr * LDK + (j ^ CARVE_QX(rr))] = (T)(rr < R ? a.Vb[j * R + rr] : 0.0f);
-    if constexpr (!SW) sVwT[rr * LDK + (j ^ CARVE_QX(rr))] = (T)(rr < R ? a.Vw[j * R + rr] : 0.0f);
+  typedef RowTile<T, D> RT;
+  typedef SmallTile<T> ST;
+  static constexpr bool GATED = (VAR & kVarGated) != 0;
+  static constexpr bool SW = (VAR & kVarScalarW) != 0;
+  static constexpr bool ACT = (VAR & kVarAct) != 0;
+  static constexpr int NT = bwd_threads(D);
+  static constexpr int NW = NT / 64;
+  static constexpr int NJT = D / 16;
+  static constexpr int RF = fold_rows(RP, VAR);
+  static constexpr int NRT = RF / 16, NRB = RP / 16;
+  typedef RowTile<T, RF> RY;
+  static constexpr int VEC = 16 / sizeof(T);
+  static constexpr int QB = 4 * (int)sizeof(T);   // bytes of a quad
+  static constexpr AdjLds lay = adj_lds<T, D, RP, VAR, NBK>();
+  // dtau tiles: wave w takes fold row tiles w % NRW + k NRW (NVS of them) of
+  // token tiles w / NRW, + NTW, ...
+  static constexpr int NRW = NRT < NW ? NRT : NW;
+  static constexpr int NVS = NRT / NRW;
+  static constexpr int NTW = NW / NRW;
+  static_assert(NRT % NRW == 0 && NW % NRW == 0, "whole tiles per wave");
+  // dF parts of the glue: rows of RF elements, quad q of row j at q ^ (j mod 16)
+  // (bf16; conflict-free for the row reads and the result-quad writes), or 16
+  // bytes of padding (f32, one part)
+  static constexpr bool SPLIT = sizeof(T) == 2;
+  static constexpr int LDF = SPLIT ? RF : RF + 4;
+  static __device__ __forceinline__ int df_at(int j, int r) {
+    return j * LDF + (SPLIT ? (r ^ (4 * (j & 15 & (RF / 4 - 1)))) : r);
   }
-  // Vb / Vw operand quads (lane (g, c): V[16 w + c][16 ks + 4 g + e]) are read
-  // from sVbT / sVwT with the transposing load where needed; the identity
-  // operand (lane (g, c): I[4 g + e][c]) is rebuilt where needed.
-  if (GATED)
-    for (int x = tid; x < D; x += NT) {
-      sGate[x] = -expf(a.A[h * D + x]);
-      sGate[D + x] = a.tau_f[h * D + x];
-    }
-#define CARVE_FVB(KS_) CARVE_LDTR(sVbT, LDK, 16 * (KS_), 16 * w)
-#define CARVE_FVW(KS_) CARVE_LDTR(sVwT, LDK, 16 * (KS_), 16 * w)
-#define CARVE_FI() Qd::cvt(f32x4{4 * g == c ? 1.0f : 0.0f, 4 * g + 1 == c ? 1.0f : 0.0f, \
-                                 4 * g + 2 == c ? 1.0f : 0.0f, 4 * g + 3 == c ? 1.0f : 0.0f})
-  __syncthreads();
 
-  // ---- persistent accumulators --------------------------------------------------
-  const size_t soff = (size_t)bh * D * D;
-  f32x4 dSt[NJT];                 // dS[v = 16 w + c][j = 16 jt + 4 g + i]
-  for (int jt = 0; jt < NJT; ++jt)
-    dSt[jt] = a.dS_T ? gload4(a.dS_T + soff + (16 * w + c) * D + 16 * jt + 4 * g) : zero4();
-  f32x4 dF[NRT];                  // dF[r = 16 rt + 4 g + i][j = 16 w + c]
-  // GATED: this lane's sums over its tokens of dg g and df (channels 16 w + 4 g + i)
-  f32x4 gaccA = zero4(), gaccT = zero4();
-  for (int rt = 0; rt < NRT; ++rt) dF[rt] = zero4();
-
-  // ---- prefetch registers: the next block to process (reverse order) and, at
-  // the last block of a chunk, the fold F of the next chunk.  Every block
-  // starts with one wait for all of this wave's memory operations, issued at
-  // least a block earlier.
-  constexpr int NTAU = 16 * R2 / VEC;   // 16-byte vectors of a block's tau
-  constexpr int NTV = (NTAU + NT - 1) / NT;
-  constexpr int NFV = (R2 * D / VEC + NT - 1) / NT;   // 16-byte vectors of F per thread
-  u32x4 ptau[NTV], pF[NFV];
-  // token tiles k, q, bx (KREC: the recorded erase gate), v, dO and (not SW) wx
-  // of a block: NS * 16 rows of D elements read as 16-byte vectors (whole rows,
-  // coalesced) and staged through LDS
-  constexpr int NC = D / VEC;                    // 16-byte chunks per row
-  constexpr int NSV = NS * 16 * NC;              // vectors of the tiles
-  constexpr int NSTG = (NSV + NT - 1) / NT;      // per thread
-  static_assert((16 * NC) % 64 == 0 || NSV % NT == 0, "tile index uniform per wave");
-  static_assert(!ACT || (16 * NC) % 64 == 0, "a staged row's chunks in one wave (row sums over lanes)");
-  u32x4 pstg[NSTG];
-  // g (KREC: the recorded E) of a block: 16 rows of D floats, one 16-byte
-  // vector per thread
-  constexpr int NGC = D / 4;                     // 16-byte chunks per g row
-  static_assert(16 * NGC == NT, "one g vector per thread");
-  quad ptm, ppm, psbq[NJT];
-  f32x4 pg;
-  u32x4 pfv;        // a 16-byte vector of the block's f rows (GATED)
-  T pbeta = (T)0.0f, pws = (T)0.0f;   // beta and (SW) the write logit of token tid
-  // The prefetch of a block is issued in two parts during the previous block's
-  // value- and key-side steps (which hardly use the memory pipeline), not at
-  // its top, where issuing it would stall the waves: LOADA (token tiles, tau,
-  // T, P, retention, beta, g) and LOADS (the block start state, once the
-  // current one has had its last use).
-#define CARVE_BWD_LOADS(GB_)                                                                  \
-  do {                                                                                        \
-    const int ch_ = (GB_) / nbc, bc_ = (GB_) % nbc;                                           \
-    const char* rc_ = recb + (size_t)ch_ * cr.total;                                          \
-    const T* sv_ = reinterpret_cast<const T*>(rc_ + cr.S) + (size_t)bc_ * NJT * NT * 4 + tid * 4; \
-    for (int jt_ = 0; jt_ < NJT; ++jt_) psbq[jt_] = Qd::ld(sv_ + (size_t)jt_ * NT * 4);        \
-  } while (0)
-#define CARVE_BWD_LOADA(GB_)                                                                  \
-  do {                                                                                        \
-    const int ch_ = (GB_) / nbc, bc_ = (GB_) % nbc;                                           \
-    const char* rc_ = recb + (size_t)ch_ * cr.total;                                          \
-    const int tb_ = ch_ * L + 16 * bc_;                                                       \
-    const int e_ = (tb_ + c) * rs + 16 * w + 4 * g;                                           \
-    const T* tau_ = reinterpret_cast<const T*>(rc_ + cr.Tau) + 16 * bc_ * R2;                 \
-    for (int u_ = 0; u_ < NTV; ++u_) {                                                        \
-      const int x_ = tid + u_ * NT;                                                           \
-      if (x_ < NTAU) ptau[u_] = *reinterpret_cast<const u32x4*>(tau_ + x_ * VEC);             \
-    }                                                                                         \
-    if (tid < 64) {                                                                           \
-      ptm = Qd::ld(reinterpret_cast<const T*>(rc_ + cr.Tm) + bc_ * 256 + 4 * tid);            \
-      ppm = Qd::ld(reinterpret_cast<const T*>(rc_ + cr.P) + bc_ * 256 + 4 * tid);             \
-    }                                                                                         \
-    if (tid < 16) {                                                                           \
-      pbeta = beta[(tb_ + tid) * H];                                                          \
-      if constexpr (SW) pws = wx[(tb_ + tid) * H];                                            \
-    }                                                                                         \
-    for (int u_ = 0; u_ < NSTG; ++u_) {                                                       \
-      const int x_ = tid + u_ * NT;                                                           \
-      if (NSV % NT != 0 && x_ >= NSV) break;                                                  \
-      const int s_ = x_ / (16 * NC), t_ = (x_ / NC) % 16, k_ = x_ % NC;                       \
-      if (KREC && s_ == 2) {                                                                  \
-        /* the recorded erase gate of the block (rows of D) in place of bx */                 \
-        pstg[u_] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const T*>(rc_ + cr.Sig) +   \
-                                                   (16 * bc_ + t_) * D + k_ * VEC);            \
-      } else {                                                                                \
-        const T* src_ = s_ == 0 ? k : s_ == 1 ? q : s_ == 2 ? bx : s_ == 3 ? v : s_ == 4 ? dO : wx; \
-        pstg[u_] = *reinterpret_cast<const u32x4*>(src_ + (tb_ + t_) * rs + k_ * VEC);         \
-      }                                                                                       \
-    }                                                                                         \
-    if constexpr (GATED) {                                                                    \
-      if (tid < 16 * NC) pfv = *reinterpret_cast<const u32x4*>(fl + (tb_ + tid / NC) * rs + (tid % NC) * VEC); \
-    } else {                                                                                  \
-      /* the recorded E of the block in place of g */                                          \
-      pg = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(rc_ + cr.E) +         \
-                                           (16 * bc_ + tid / NGC) * D + 4 * (tid % NGC));      \
-    }                                                                                         \
-    (void)e_;                                                                                 \
-  } while (0)
-#define CARVE_BWD_LOADF(CH_)                                                                  \
-  do {                                                                                        \
-    const T* src_ = reinterpret_cast<const T*>(recb + (size_t)(CH_) * cr.total + cr.F);       \
-    for (int u_ = 0; u_ < NFV; ++u_) {                                                        \
-      const int x_ = tid + u_ * NT;                                                           \
-      if (x_ < R2 * D / VEC) pF[u_] = *reinterpret_cast<const u32x4*>(src_ + x_ * VEC);       \
-    }                                                                                         \
-  } while (0)
-  // [Ub; Uw] operand quads of the glue, lane (g, c): U[16 rt + 4 g + e][16 w + c]
-  // (rows past R are zero), loaded once for the whole call
-  quad fU[NRT];
-  for (int rt = 0; rt < NRT; ++rt) {
-    const float* src = rt < RP / 16 ? a.Ub : a.Uw;
-    f32x4 tu;
-    for (int e = 0; e < 4; ++e) {
-      const int rl = 16 * (rt % (RP / 16)) + 4 * g + e;
-      tu[e] = rl < R ? src[rl * D + 16 * w + c] : 0.0f;
-    }
-    fU[rt] = Qd::cvt(tu);
+  const BwdArgs& a;
+  const int bh;
+  char* smem;
+  int tid, lane, w, g, c;
+  int H, L, R, nch, mpc, rs, h;
+  ChunkRec cr;
+  size_t bh0, bh1;
+  const char* recb;
+  T* opnd;
+  // gate constants of the wave's keys (GATED), behind the operand quads
+  __device__ __forceinline__ float* gate(int k) const {
+    return reinterpret_cast<float*>(opnd + adj_opnd_quads(D, 2 * RP) * 4) + ((size_t)k * NT + tid) * 4;
   }
-  const int ngb = nch * nbc;
-  const int* rdy = ready + (size_t)bh * nch;
-  // chunks >= acq_lo have been acquired by this wave; acq_lo = -1 after a wait
-  // ran out of its bound (never in a correct launch)
-  int acq_lo = nch;
-#define CARVE_BWD_READY(CH_)                                                                  \
-  do {                                                                                        \
-    if ((CH_) < acq_lo) {                                                                     \
-      const int lo_ = acquire_ready(rdy, (CH_), a.wait_limit);                                \
-      if (lo_ > (CH_)) {                                                                      \
-        acq_lo = -1;                                                                          \
-        if ((threadIdx.x & 63) == 0)                                                          \
-          __hip_atomic_store(timeout_word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);    \
-        for (int jt_ = 0; jt_ < NJT; ++jt_) dSt[jt_] = f32x4{__builtin_nanf(""), __builtin_nanf(""), \
-                                                             __builtin_nanf(""), __builtin_nanf("")}; \
-      } else {                                                                                \
-        acq_lo = lo_;                                                                         \
-      }                                                                                       \
-    }                                                                                         \
-  } while (0)
-  CARVE_BWD_READY(nch - 1);
-  CARVE_BWD_LOADA(ngb - 1);
-  CARVE_BWD_LOADS(ngb - 1);
-  CARVE_BWD_LOADF(nch - 1);
 
-  // pending dq / dF update of the last processed block (its BQ step)
-  f32x4 pdqp = zero4();
-  quad pqq = Qd::cvt(zero4());
-  int pe0 = 0;
-#define CARVE_BWD_BQ()                                                                        \
-  do {                                                                                        \
-    f32x4 acc_ = pdqp;                                                                        \
-    for (int rp = 0; rp < R2 / 32; ++rp)                                                      \
-      acc_ = Qd::mma32(Qd::ld_tr(sF, LDD, 32 * rp, 16 * w, g, c), Qd::ld_tr(sF, LDD, 32 * rp + 16, 16 * w, g, c), \
-                       Qd::ld(sdY + c * LDR + 32 * rp + 4 * g), Qd::ld(sdY + c * LDR + 32 * rp + 16 + 4 * g), acc_); \
-    Qd::st(dq + pe0, Qd::cvt(acc_));                                                          \
-    const quad qT_ = Qd::cvt(Qd::mma16(pqq, CARVE_FI(), zero4()));   /* q[t = 4g + i][j = 16 w + c] */ \
-    for (int rt = 0; rt < NRT; ++rt) dF[rt] = Qd::mma16(Qd::ld_tr(sdY, LDR, 0, 16 * rt, g, c), qT_, dF[rt]); \
-  } while (0)
-#define CARVE_BWD_GAM()                                                                       \
-  do {                                                                                        \
-    f32x4 gm_[NJT];                                                                           \
-    for (int jt_ = 0; jt_ < NJT; ++jt_) gm_[jt_] = *reinterpret_cast<const f32x4*>(sGam + 16 * jt_ + 4 * g); \
-    for (int jt_ = 0; jt_ < NJT; ++jt_) dSt[jt_] *= gm_[jt_];                                 \
-  } while (0)
-#pragma unroll 1
-  for (int gb = ngb - 1; gb >= 0; --gb) {
-    const int ch = gb / nbc, bc = gb % nbc;
-    const char* rc = recb + (size_t)ch * cr.total;
+  // tile images of a block in registers on their way to LDS
+  static constexpr int W = 16 * NBK;
+  static constexpr int NVK = (int)(image_bytes<T, D>(W) / 16);        // vectors of one image
+  static constexpr int NKV = (3 * NVK + NT - 1) / NT, NUV = (NVK + NT - 1) / NT;
+  static constexpr int NVC = (int)(ctile_bytes<T>(NBK) / 16);
+  static constexpr int NCV = (NVC + NT - 1) / NT;
+  static constexpr int NVO = W * D / VEC;                             // vectors of the block's dO rows
+  static constexpr int NOV = (NVO + NT - 1) / NT;
+
+  // Opaque copies of the lane coordinates: addresses derived from them are
+  // recomputed in every step instead of being kept live across steps and blocks.
+  __device__ __forceinline__ void fresh() { asm volatile("" : "+v"(tid), "+v"(g), "+v"(c) : : "memory"); }
+  // makes the compiler wait for a loaded value here
+  template <typename V>
+  static __device__ __forceinline__ void arrived(V& v) { asm volatile("" : "+v"(v)); }
+  __device__ __forceinline__ T* lds(size_t off) const { return reinterpret_cast<T*>(smem + off); }
+  __device__ __forceinline__ float* ldf(size_t off) const { return reinterpret_cast<float*>(smem + off); }
+  __device__ __forceinline__ quad fI() const {
+    return Qd::cvt(f32x4{4 * g == c ? 1.0f : 0.0f, 4 * g + 1 == c ? 1.0f : 0.0f, 4 * g + 2 == c ? 1.0f : 0.0f,
+                         4 * g + 3 == c ? 1.0f : 0.0f});
+  }
+  // the transpose of a tile in the result layout, in the token dtype: lane
+  // (g, c) receives X[c][4 g + e]
+  __device__ __forceinline__ quad tposed(quad x) const { return Qd::cvt(Qd::mma16(x, fI(), zero4())); }
+
+  struct Pre {          // prefetched data of the next block
+    u32x4_t k[NKV], cc[NCV], u[NUV], o[NOV];
+    f32x4 wg[NBK];
+    quad v[NBK];
+    f32x4 gam;
+    float beta, ws;
+  };
+  // persistent per-wave values
+  struct State {
+    f32x4 dS[NJT];      // dS[v = 16 w + c][j = 16 jt + 4 g + i]
+    f32x4 gA, gT;       // GATED: sums over this lane's tokens of dg g and df
+  };
+
+  // vector u of this thread out of N: threads past the end repeat the last one
+  // (the same load and the same LDS write, without a branch around either)
+  template <int N>
+  __device__ __forceinline__ int vec(int u) const {
+    const int x = tid + u * NT;
+    return (u + 1) * NT <= N ? x : x < N ? x : N - 1;
+  }
+  __device__ __forceinline__ const char* rec_of(int ch) const { return recb + (size_t)ch * cr.total; }
+
+  // loads of block (ch, m) into registers
+  __device__ __forceinline__ void load_tiles(Pre& p, int ch, int m) const {
+    const RecBuf rc(rec_of(ch), cr.total);
+    for (int u = 0; u < NKV; ++u) p.k[u] = rc.template ld<u32x4_t>(cr.K + 3 * image_bytes<T, D>(W) * m, 16 * vec<3 * NVK>(u));
+    for (int u = 0; u < NCV; ++u) p.cc[u] = rc.template ld<u32x4_t>(cr.C + ctile_bytes<T>(NBK) * m, 16 * vec<NVC>(u));
+  }
+  __device__ __forceinline__ void load_uo(Pre& p, int ch, int m) const {
+    const RecBuf rc(rec_of(ch), cr.total);
+    for (int u = 0; u < NUV; ++u) p.u[u] = rc.template ld<u32x4_t>(cr.U + image_bytes<T, D>(W) * m, 16 * vec<NVK>(u));
+    const T* so = reinterpret_cast<const T*>(a.dO) + bh0 + (size_t)((ch * L + m * W) * rs);
+    for (int u = 0; u < NOV; ++u) {
+      const int x = vec<NVO>(u);
+      p.o[u] = *reinterpret_cast<const u32x4_t*>(so + (x / (D / VEC)) * rs + (x % (D / VEC)) * VEC);
+    }
+  }
+  __device__ __forceinline__ void load_vals(Pre& p, int ch, int m) const {
+    const RecBuf rc(rec_of(ch), cr.total);
+    for (int tt = 0; tt < NBK; ++tt) {
+      if constexpr (!SW) p.wg[tt] = rc.template ld<f32x4>(cr.W + (m * NBK + tt) * NT * 16, tid * 16);
+      p.v[tt] = rc.template ld<quad>(cr.V + (m * NBK + tt) * NT * QB, tid * QB);
+    }
+  }
+  // registers -> LDS
+  __device__ __forceinline__ void put_tiles(const Pre& p) const {
+    u32x4_t* dk = reinterpret_cast<u32x4_t*>(smem + lay.Kt);
+    for (int u = 0; u < NKV; ++u) dk[vec<3 * NVK>(u)] = p.k[u];
+    u32x4_t* dc = reinterpret_cast<u32x4_t*>(smem + lay.C);
+    for (int u = 0; u < NCV; ++u) dc[vec<NVC>(u)] = p.cc[u];
+    *reinterpret_cast<f32x4*>(smem + lay.Gam + 16 * vec<D / 4>(0)) = p.gam;
+    ldf(lay.Beta)[vec<W>(0)] = p.beta;
+    if constexpr (SW) ldf(lay.Ws)[vec<W>(0)] = p.ws;
+  }
+  __device__ __forceinline__ void load_scalars(Pre& p, int ch, int m) const {
+    const RecBuf rc(rec_of(ch), cr.total);
+    p.gam = rc.template ld<f32x4>(cr.Gam + m * NBK * D * 4, 16 * vec<D / 4>(0));
+    p.beta = rc.template ld<float>(cr.Beta + m * W * 4, 4 * vec<W>(0));
+    if constexpr (SW) p.ws = rc.template ld<float>(cr.Beta + (L + m * W) * 4, 4 * vec<W>(0));
+  }
+  __device__ __forceinline__ void put_uo(const Pre& p) const {
+    u32x4_t* du = reinterpret_cast<u32x4_t*>(smem + lay.U);
+    for (int u = 0; u < NUV; ++u) du[vec<NVK>(u)] = p.u[u];
+    for (int u = 0; u < NOV; ++u) {
+      stage_vec<T, D, false, false>(lds(lay.dO), vec<NVO>(u), p.o[u]);
+    }
+  }
+
+  // One tile of a block evaluated tile by tile: its rows of the images, its P
+  // and T tiles and its dO rows straight into LDS (the layout of a block of one
+  // tile), its gates into p.
+  __device__ __forceinline__ void load_tile_direct(Pre& p, int ch, int m, int i) const {
+    const RecBuf rc(rec_of(ch), cr.total);
+    constexpr int NV1 = (int)(image_bytes<T, D>(16) / 16);
+    for (int y = 0; y < 4; ++y) {
+      const unsigned src = (y < 3 ? cr.K + (3 * m + y) * image_bytes<T, D>(W) : cr.U + m * image_bytes<T, D>(W)) + i * image_bytes<T, D>(16);
+      const size_t dst = y == 0 ? lay.Kt : y == 1 ? lay.Qt : y == 2 ? lay.Ki : lay.U;
+      for (int x = tid; x < NV1; x += NT)
+        reinterpret_cast<u32x4_t*>(smem + dst)[x] = rc.template ld<u32x4_t>(src, 16 * x);
+    }
+    constexpr int NVT = ST::N * (int)sizeof(T) / 16;
+    for (int x = tid; x < 2 * NVT; x += NT) {
+      const int t = x < NVT ? tri_incl(i, i) : tiles_p(NBK) + tiles_a(NBK) + i;
+      reinterpret_cast<u32x4_t*>(smem + lay.C)[x] =
+          rc.template ld<u32x4_t>(cr.C + ctile_bytes<T>(NBK) * m, t * ST::N * (int)sizeof(T) + 16 * (x % NVT));
+    }
+    const T* so = reinterpret_cast<const T*>(a.dO) + bh0 + (size_t)((ch * L + m * W + 16 * i) * rs);
+    for (int x = tid; x < 16 * D / VEC; x += NT)
+      stage_vec<T, D, false, false>(lds(lay.dO), x, *reinterpret_cast<const u32x4_t*>(so + (x / (D / VEC)) * rs + (x % (D / VEC)) * VEC));
+    if constexpr (!SW) p.wg[0] = rc.template ld<f32x4>(cr.W + (m * NBK + i) * NT * 16, tid * 16);
+    p.v[0] = rc.template ld<quad>(cr.V + (m * NBK + i) * NT * QB, tid * QB);
+    if (tid < D / 4)
+      *reinterpret_cast<f32x4*>(smem + lay.Gam + 16 * tid) = rc.template ld<f32x4>(cr.Gam + (m * NBK + i) * D * 4, 16 * tid);
+    if (tid < 16) {
+      ldf(lay.Beta)[tid] = rc.template ld<float>(cr.Beta + (m * W + 16 * i) * 4, 4 * tid);
+      if constexpr (SW) ldf(lay.Ws)[tid] = rc.template ld<float>(cr.Beta + (L + m * W + 16 * i) * 4, 4 * tid);
+    }
+  }
+
+  // Adjoint of one block of NB tiles whose data is in LDS (after a barrier) and
+  // p (wg, v): tiles tile0 .. tile0 + NB - 1 of chunk ch.  With next >= 0
+  // (block index of the chunk nch_) the next block's data is loaded meanwhile
+  // and put into LDS before the end; the caller's barrier publishes it.
+  // wait_ch >= 0: wave 0 waits for that chunk's flag and leaves it in Ctl.
+  template <int NB>
+  __device__ __forceinline__ void block(State& s, Pre& p, f32x4 (&dF)[NRT], quad (&fU)[NRT], int ch, int tile0, int wait_ch,
+                                        bool& timed_out, int nx_ch_same, int nx_m) {
+    constexpr int W = 16 * NB;   // tokens of this block (the images in LDS have W rows)
+    constexpr int NTP = tiles_p(NB), NTA = tiles_a(NB);
+    fresh();
+    const RecBuf rc(rec_of(ch), cr.total);
+    const int t0 = ch * L + 16 * tile0;
+    T* sKt = lds(lay.Kt);
+    T* sQt = lds(lay.Qt);
+    T* sKi = lds(lay.Ki);
+    T* sU = lds(lay.U);
+    T* sdO = lds(lay.dO);
+    T* sdM = lds(lay.dM);
+    T* sR = lds(lay.R);
+    T* sC = lds(lay.C);
+    T* sdY = lds(lay.dY);
+    float* sDbeta = ldf(lay.Dbeta) + w * W;
+    float* sBeta = ldf(lay.Beta);
+    float* sGam = ldf(lay.Gam);
+    const auto e0 = [&](int tt) { return (t0 + 16 * tt + c) * rs + 16 * w + 4 * g; };
+
+    // ---- B1: value side (value tile w; rows t = 16 tt + 4 g + i, column v = 16 w + c)
+    // S' of the block for B2, loaded ahead of this step's stores (transposed operand quads)
+    quad sS[NJT];
     {
-      // opaque copies of the lane coordinates: values derived from them
-      // (addresses, masks) are recomputed in every block instead of being
-      // hoisted out of the loops and kept live (which would spill)
-      int tid_ = tid, g_ = g, c_ = c, w_ = w;
-      asm volatile("" : "+v"(tid_), "+v"(g_), "+v"(c_), "+v"(w_));
-      const int tid = tid_, g = g_, c = c_, w = w_;
-      const int lane = tid & 63;
-      (void)lane;
-      const int tb = ch * L + 16 * bc;   // first token of the block
-      const int e0 = (tb + c) * rs + 16 * w + 4 * g;
-
-      // -- BK1 (a): this block's data (prefetched a block ago) ------------------------
-      vm_wait_all();
-      u32x4 ltau[NTV];
-      for (int u = 0; u < NTV; ++u) ltau[u] = ptau[u];
-      const quad ltm = ptm, lpm = ppm;
-      const T lbeta = pbeta, lws = pws;
-      quad sbq[NJT];   // block start state, wave layout: S[16 w + c][16 jt + 4 g + e]
-      for (int jt = 0; jt < NJT; ++jt) sbq[jt] = psbq[jt];
-      {
-        // S of the block into its own region now (the last block's key side,
-        // its only reader, ended two barriers ago); dS' waits for the first
-        // barrier (its region holds the glue's dF parts until then)
-        const int hx = SXH ? hswz128(c) : 0;
-        for (int jt = 0; jt < NJT; ++jt) Qd::st(sSx + (16 * w + c) * LDSX + ((16 * jt + 4 * g) ^ hx), sbq[jt]);
+      for (int vt = 0; vt < NJT; ++vt) sS[vt] = rc.template ld<quad>(cr.S + (tile0 * NJT + vt) * NT * QB, tid * QB);
+    }
+    quad dOq[NB], nq[NB], dzwT[NB], dvT[NB];   // dO, -dR (K = t operands); dz_w, dv as token rows
+    {
+      quad dMq[NJT];
+      for (int jt = 0; jt < NJT; ++jt) {
+        s.dS[jt] *= *reinterpret_cast<const f32x4*>(sGam + 16 * jt + 4 * g);
+        dMq[jt] = Qd::cvt(s.dS[jt]);
+        Qd::st(sdM + RT::at(16 * w + c, 16 * jt, 4 * g), dMq[jt]);
       }
-      u32x4 lstg[NSTG];
-      for (int u = 0; u < NSTG; ++u) lstg[u] = pstg[u];
-      const f32x4 lg_row = pg;   // a row vector of g (staged below)
-      const u32x4 lf_row = pfv;  // GATED: a row vector of f
-      if (bc == nbc - 1) {
-        // first block of a chunk in reverse order: the chunk's F into LDS (the
-        // previous chunk's last read of sF was before its glue barriers)
-        for (int u = 0; u < NFV; ++u) {
-          const int x = tid + u * NT;
-          if (x < R2 * D / VEC) {
-            const int rr = x / (D / VEC), j = (x % (D / VEC)) * VEC;
-            *reinterpret_cast<u32x4*>(sF + rr * LDD + j) = pF[u];
-          }
-        }
-      }
-      // the next block's prefetch (below) reads chunk ch - 1's record at a
-      // chunk's last block: wait until the recompute has published it
-      if (bc == 0 && ch > 0) CARVE_BWD_READY(ch - 1);
-
-      // -- BQ of the previous block (overlaps the loads above) -------------------
-      if (bc < nbc - 1) CARVE_BWD_BQ();
-
-      // -- BK1 (c): stage the block record; recompute the key side; S, dS' -> LDS
-      for (int u = 0; u < NTV; ++u) {
-        const int x = tid + u * NT;
-        if (x < NTAU) {
-          const int t = x / (R2 / VEC), r = (x % (R2 / VEC)) * VEC;
-          *reinterpret_cast<u32x4*>(sTau + t * LDR + r) = ltau[u];
-        }
-      }
-      if (tid < 64) {
-        const int t = tid >> 2, s4 = 4 * (tid & 3);
-        Qd::st(sTm + t * LDB + s4, ltm);
-        Qd::st(sP + t * LDB + s4, lpm);
-      }
-      if (tid < 16) {
-        sBeta[tid] = (float)lbeta;
-        if constexpr (SW) sBeta[16 + tid] = sigmoid_f((float)lws);
-      }
-      // token tiles -> LDS: 16-byte chunk kk of row t goes to chunk kk ^ (t mod NC)
-      // (a row-dependent swizzle instead of padding: the 16 rows a wave reads in
-      // one quad load fall into distinct banks)
-      for (int u = 0; u < NSTG; ++u) {
-        const int x = tid + u * NT;
-        if (NSV % NT != 0 && x >= NSV) break;
-        const int s_ = x / (16 * NC), t = (x / NC) % 16, kk = x % NC;
-        *reinterpret_cast<u32x4*>(sStg + (s_ * 16 + t) * D + (kk ^ (t & (NC - 1))) * VEC) = lstg[u];
-        if constexpr (ACT) {
-          // k (s_ = 0) and q (s_ = 1) rows: the row's NC chunks are in NC
-          // consecutive lanes, and s_ is uniform over a wave
-          if (s_ < 2) {
-            const float inv = act_row_inv_norm<T, NC>(lstg[u]);
-            if (kk == 0) sInv[s_ * 16 + t] = inv;
-          }
-        }
-      }
-      if constexpr (GATED) {
-        if (tid < 16 * NC) {
-          const int t = tid / NC, kk = tid % NC;
-          *reinterpret_cast<u32x4*>(sFs + t * D + (kk ^ (t & (NC - 1))) * VEC) = lf_row;
-        }
-      } else {
-        const int t = tid / NGC, kk = tid % NGC;
-        *reinterpret_cast<f32x4*>(sGs + t * D + 4 * (kk ^ (t & (NGC - 1)))) = lg_row;
-      }
-      // the previous block's state gradient with respect to S (the factor
-      // e^{rho} of its sGam, which the form step below rewrites); deferred
-      // from that block's end, where its loads would wait one by one
-      if (bc < nbc - 1) CARVE_BWD_GAM();
-      __syncthreads();
-      // the chunks started so far, for the pacing of the recompute
-      if (bc == nbc - 1 && tid == 0) __hip_atomic_store(pos, nch - ch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      // this wave's quads of the token tiles (row t = c, elements 16 w + 4 g ..
-      // + 3) and of tau_b; read before the barrier that ends this step, so the
-      // value-side step may overwrite the staging region
-      quad kq, qq, lbx, vq, wxq, dOq, ltq[NRB];
-      quad vraw;  // ACT: the raw value quad (for SiLU' of dv)
-      f32x4 lg;
-      {
-        const int by = (16 * w + 4 * g) * (int)sizeof(T);
-        const int off = ((((by >> 4) ^ (c & (NC - 1))) << 4) | (by & 15)) / (int)sizeof(T);
-        if constexpr (GATED) {
-          const f32x4 fv = Qd::f32(Qd::ld(sFs + c * D + off));
-          const f32x4 na = *reinterpret_cast<const f32x4*>(sGate + 16 * w + 4 * g);
-          const f32x4 tf = *reinterpret_cast<const f32x4*>(sGate + D + 16 * w + 4 * g);
-          for (int i = 0; i < 4; ++i) lg[i] = na[i] * softplus_f(fv[i] + tf[i]);
-        } else {
-          lg = *reinterpret_cast<const f32x4*>(sGs + c * D + 4 * ((4 * w + g) ^ (c & (NGC - 1))));
-        }
-        const T* r0 = sStg + c * D + off;
-        kq = Qd::ld(r0);
-        qq = Qd::ld(r0 + 16 * D);
-        lbx = Qd::ld(r0 + 32 * D);
-        vq = Qd::ld(r0 + 48 * D);
-        dOq = Qd::ld(r0 + 64 * D);
-        if constexpr (!SW) wxq = Qd::ld(r0 + 80 * D);
-        if constexpr (ACT) {
-          kq = Qd::cvt(silu4(Qd::f32(kq)) * sInv[c]);
-          qq = Qd::cvt(silu4(Qd::f32(qq)) * sInv[16 + c]);
-          vraw = vq;
-          vq = Qd::cvt(silu4(Qd::f32(vq)));
-        }
-        if constexpr (!KREC)
-          for (int ks = 0; ks < NRB; ++ks) ltq[ks] = Qd::ld(sTau + c * LDR + 16 * ks + 4 * g);
-      }
-      // key-side factors kept for the adjoint in the token dtype (quads)
-      quad Eq, Eiq, sigq;
-      {
-        const f32x4 kv = Qd::f32(kq), qv = Qd::f32(qq);
-        f32x4 kt, qt, ki, E, Ei, sig, gp;
-        if constexpr (KREC) {
-          // E and the erase gate as the recompute formed them (staged in place
-          // of g and bx); Ei from E as there, so every tile matches its T and P
-          sig = Qd::f32(lbx);
-          for (int i = 0; i < 4; ++i) {
-            E[i] = lg[i];
-            Ei[i] = fast_rcp(E[i]);
-          }
-        } else {
-          f32x4 z = zero4();
-          for (int ks = 0; ks < NRB; ++ks) z = Qd::mma16(CARVE_FVB(ks), ltq[ks], z);
-          const f32x4 bxv = Qd::f32(lbx);
-          for (int i = 0; i < 4; ++i) {
-            float sp, sg;
-            softplus_sigmoid(z[i] + bxv[i], sp, sg);
-            sig[i] = sg;
-            const float lam = row_scan(lg[i] - sp);
-            const float rho = 0.5f * row_bcast15(lam);
-            E[i] = fast_exp(lam - rho);
-            Ei[i] = fast_exp(rho - lam);
-          }
-        }
-        for (int i = 0; i < 4; ++i) {
-          // e^{lam_{-1} - rho} = e^{-rho} = Ei of the last token
-          kt[i] = kv[i] * row_shr1(E[i], row_bcast15(Ei[i]));
-          qt[i] = qv[i] * E[i];
-          ki[i] = kv[i] * Ei[i];
-          gp[i] = row_bcast15(E[i]);   // gam = e^{lam_15 - rho} = e^{rho}
-        }
-        if (c == 0) *reinterpret_cast<f32x4*>(sGam + 16 * w + 4 * g) = gp;
-        Eq = Qd::cvt(E);
-        Eiq = Qd::cvt(Ei);
-        sigq = Qd::cvt(sig);
-        const int ro = c * LDK + 16 * w + ((4 * g) ^ CARVE_QX(c));
-        Qd::st(sKt + ro, Qd::cvt(kt));
-        Qd::st(sQt + ro, Qd::cvt(qt));
-        Qd::st(sKi + ro, Qd::cvt(ki));
-      }
-      {
-        // row 16 w + c: its swizzle term depends on c only
-        const int hx = SXH ? hswz128(c) : 0;
-        for (int jt = 0; jt < NJT; ++jt) {
-          const int o = (16 * w + c) * LDSX + ((16 * jt + 4 * g) ^ hx);
-          Qd::st(sdSx + o, Qd::cvt(dSt[jt]));
-        }
-      }
-      if constexpr (KREC) {
-        // dS' becomes dM = dS' diag(gam) in place, gam = e^{rho} = E of the
-        // block's last token (row 15 of the staged record: the same values
-        // the form step above writes to sGam for its own key tile)
-        f32x4 gm[NJT];
-        for (int jt = 0; jt < NJT; ++jt)
-          gm[jt] = *reinterpret_cast<const f32x4*>(sGs + 15 * D + 4 * ((4 * jt + g) ^ (15 & (NGC - 1))));
-        for (int jt = 0; jt < NJT; ++jt) dSt[jt] *= gm[jt];
-      }
-      __syncthreads();
-
-      // -- BV: value-side adjoint (value tile w, rows t = 4 g + i, column v = 16 w + c)
-      // prefetch (part A) of the next block, and at a chunk's last block the
-      // next chunk's F
-      CARVE_BWD_LOADA(gb > 0 ? gb - 1 : 0);
-      if (bc == 0) CARVE_BWD_LOADF(ch > 0 ? ch - 1 : 0);
-      {
-        const f32x4 vv = Qd::mma16(vq, CARVE_FI(), zero4());
-        const f32x4 dOc = Qd::mma16(dOq, CARVE_FI(), zero4());
-        f32x4 wgt;
-        if constexpr (SW) {
-          wgt = *reinterpret_cast<const f32x4*>(sBeta + 16 + 4 * g);   // one gate per token
-        } else {
-          f32x4 zw = zero4();
-          for (int ks = 0; ks < NRB; ++ks)
-            zw = Qd::mma16(Qd::ld(sTau + c * LDR + RP + 16 * ks + 4 * g), CARVE_FVW(ks), zw);
-          zw = Qd::mma16(wxq, CARVE_FI(), zw);
-          for (int i = 0; i < 4; ++i) wgt[i] = sigmoid_f(zw[i]);
-        }
-        f32x4 XK = zero4();
-        const T* kr = sKt + c * LDK + ((4 * g) ^ CARVE_QX(c));
+      for (int tt = 0; tt < NB; ++tt) dOq[tt] = RT::tr(sdO, 16 * tt, 16 * w, g, c);
+      f32x4 du[NB];
+      for (int tt = 0; tt < NB; ++tt) {
+        // (two chains, added at the end: a K16 step accumulating directly on the
+        // result of a K32 step read it too early here, with wrong values in the
+        // first two rows of every quad)
+        f32x4 dp = zero4();
+        for (int i = tt; i < NB; ++i) dp = Qd::mma16(ST::tr(sC + tri_incl(i, tt) * ST::N, g, c), dOq[i], dp);
+        du[tt] = zero4();
         for (int jp = 0; jp < NJT / 2; ++jp)
-          XK = Qd::mma32(Qd::ld(kr + 32 * jp), Qd::ld(kr + 32 * jp + 16), sbq[2 * jp], sbq[2 * jp + 1], XK);
-        const f32x4 bt = *reinterpret_cast<const f32x4*>(sBeta + 4 * g);
-        f32x4 rm, rr;
+          du[tt] = Qd::mma32(Qd::ld(sKi + RT::at(16 * tt + c, 32 * jp, 4 * g)), Qd::ld(sKi + RT::at(16 * tt + c, 32 * jp + 16, 4 * g)),
+                             dMq[2 * jp], dMq[2 * jp + 1], du[tt]);
+        du[tt] += dp;
+      }
+      f32x4 dR[NB];
+      quad xq[NB];
+      for (int i = NB - 1; i >= 0; --i) {
+        f32x4 r = du[i];
+        for (int j = i + 1; j < NB; ++j) r = Qd::mma16(ST::tr(sC + (NTP + tri_strict(j, i)) * ST::N, g, c), xq[j], r);
+        dR[i] = Qd::mma16(ST::tr(sC + (NTP + NTA + i) * ST::N, g, c), Qd::cvt(r), zero4());
+        xq[i] = Qd::cvt(dR[i]);
+        nq[i] = Qd::cvt(-dR[i]);
+        // exchange: token rows of -dR for the products over the value axis
+        Qd::st(sR + RT::at(16 * i + c, 16 * w, 4 * g), tposed(nq[i]));
+      }
+      // value-side gradients (stored as token rows, 4 values per lane)
+      for (int tt = 0; tt < NB; ++tt) {
+        const f32x4 bt = *reinterpret_cast<const f32x4*>(sBeta + 16 * tt + 4 * g);
+        f32x4 wg;
+        if constexpr (SW) wg = *reinterpret_cast<const f32x4*>(ldf(lay.Ws) + 16 * tt + 4 * g);
+        else wg = p.wg[tt];
+        const f32x4 vv = Qd::f32(p.v[tt]);
+        f32x4 dvv, dzw, pr;
         for (int i = 0; i < 4; ++i) {
-          rm[i] = wgt[i] * vv[i] - XK[i];
-          rr[i] = bt[i] * rm[i];
+          const float dwv = bt[i] * dR[tt][i];
+          dvv[i] = dwv * wg[i];
+          dzw[i] = dwv * vv[i] * wg[i] * (1.0f - wg[i]);
+          pr[i] = row_scan(dR[tt][i] * wg[i] * vv[i]);   // dbeta, value part: sum over v of dR (w v)
         }
-        const f32x4 u = Qd::mma16(Qd::ld(sTm + c * LDB + 4 * g), Qd::cvt(rr), zero4());
-        // du = Ki dM^T + P^T dO with dM = dS' diag(gam)
-        f32x4 du = zero4();
-        const T* kir = sKi + c * LDK + ((4 * g) ^ CARVE_QX(c));
-        // dS' (already in LDS for the key side) becomes dM in place (KREC: in
-        // the form step): both du and the state gradient below use dM only
-        if constexpr (!KREC)
-          for (int jt = 0; jt < NJT; ++jt) dSt[jt] *= *reinterpret_cast<const f32x4*>(sGam + 16 * jt + 4 * g);
-        for (int jp = 0; jp < NJT / 2; ++jp)
-          du = Qd::mma32(Qd::ld(kir + 32 * jp), Qd::ld(kir + 32 * jp + 16), Qd::cvt(dSt[2 * jp]),
-                         Qd::cvt(dSt[2 * jp + 1]), du);
-        const quad dOcq = Qd::cvt(dOc);
-        du = Qd::mma16(Qd::ld_tr(sP, LDB, 0, 0, g, c), dOcq, du);
-        const f32x4 dR = Qd::mma16(Qd::ld_tr(sTm, LDB, 0, 0, g, c), Qd::cvt(du), zero4());
-        f32x4 dX, dwv;
-        for (int i = 0; i < 4; ++i) {
-          dX[i] = -bt[i] * dR[i];
-          dwv[i] = bt[i] * dR[i];
+        if constexpr (ACT) {
+          const f32x4 raw = Qd::f32(Qd::ld(reinterpret_cast<const T*>(a.v) + bh0 + e0(tt)));
+          dvT[tt] = Qd::cvt(Qd::mma16(Qd::cvt(dvv), fI(), zero4()) * silu_grad4(raw));
+        } else {
+          dvT[tt] = tposed(Qd::cvt(dvv));
         }
-        const quad dXq = Qd::cvt(dX);
-        // state gradient at the block start
-        for (int jt = 0; jt < NJT; ++jt) {
-          CARVE_SEQ();
-          dSt[jt] = Qd::mma32(CARVE_LDTR(sQt, LDK, 0, 16 * jt), CARVE_LDTR(sKt, LDK, 0, 16 * jt), dOcq,
-                              dXq, dSt[jt]);
-        }
-        // value-side token gradients, stored through the identity (4 values per lane)
-        f32x4 dvv, dzw;
-        for (int i = 0; i < 4; ++i) {
-          dvv[i] = dwv[i] * wgt[i];
-          dzw[i] = dwv[i] * vv[i] * wgt[i] * (1.0f - wgt[i]);
-        }
-        if constexpr (ACT)
-          Qd::st(dv + e0, Qd::cvt(Qd::mma16(Qd::cvt(dvv), CARVE_FI(), zero4()) * silu_grad4(Qd::f32(vraw))));
-        else
-          Qd::st(dv + e0, Qd::cvt(Qd::mma16(Qd::cvt(dvv), CARVE_FI(), zero4())));
-        const quad dzwq = Qd::cvt(dzw);
+        if (c == 15) *reinterpret_cast<f32x4*>(sDbeta + 16 * tt + 4 * g) = pr;
         if constexpr (SW) {
-          // the token's write-logit gradient, partial over this wave's 16 values
           f32x4 pw;
           for (int i = 0; i < 4; ++i) pw[i] = row_scan(dzw[i]);
-          if (c == 15) *reinterpret_cast<f32x4*>(sDwx + w * 16 + 4 * g) = pw;
+          if (c == 15) *reinterpret_cast<f32x4*>(ldf(lay.Dwx) + w * W + 16 * tt + 4 * g) = pw;
         } else {
-          Qd::st(dwx + e0, Qd::cvt(Qd::mma16(dzwq, CARVE_FI(), zero4())));
+          dzwT[tt] = tposed(Qd::cvt(dzw));
         }
-        // beta gradient, value part: sum over v of dR (w v - S Kt)
-        f32x4 pr;
-        for (int i = 0; i < 4; ++i) pr[i] = row_scan(dR[i] * rm[i]);
-        if (c == 15) *reinterpret_cast<f32x4*>(sDbeta + w * 16 + 4 * g) = pr;
-        // exchange, [value][token] layout
-        const int xo = (16 * w + c) * LDX + ((4 * g) ^ CARVE_QX(c));
-        Qd::st(sdRT + xo, Qd::cvt(dR));
-        Qd::st(sdOT + xo, dOcq);
-        Qd::st(suT + xo, Qd::cvt(u));
-        if constexpr (!SW) Qd::st(sdzwT + xo, dzwq);
       }
-      __syncthreads();
+    }
+    // the state gradient at the block start
+    for (int jt = 0; jt < NJT; ++jt) {
+      CARVE_SEQ();
+      f32x4 acc = s.dS[jt];
+      if constexpr (NB == 1) {
+        acc = Qd::mma32(RT::tr(sQt, 0, 16 * jt, g, c), RT::tr(sKt, 0, 16 * jt, g, c), dOq[0], nq[0], acc);
+      } else {
+        for (int tp = 0; tp < NB / 2; ++tp) {
+          acc = Qd::mma32(RT::tr(sQt, 32 * tp, 16 * jt, g, c), RT::tr(sQt, 32 * tp + 16, 16 * jt, g, c), dOq[2 * tp], dOq[2 * tp + 1], acc);
+          acc = Qd::mma32(RT::tr(sKt, 32 * tp, 16 * jt, g, c), RT::tr(sKt, 32 * tp + 16, 16 * jt, g, c), nq[2 * tp], nq[2 * tp + 1], acc);
+        }
+      }
+      s.dS[jt] = acc * *reinterpret_cast<const f32x4*>(sGam + 16 * jt + 4 * g);
+    }
+    __syncthreads();
 
-      // -- BKA: key-side adjoint (key tile w; C rows j = 16 w + 4 g + i, column t = c)
-      // prefetch (part S): the next block's start state (sbq had its last use in BV)
-      CARVE_BWD_LOADS(gb > 0 ? gb - 1 : 0);
-      f32x4 dqp;
-      {
-        const f32x4 E = Qd::f32(Eq), Ei = Qd::f32(Eiq), sig = Qd::f32(sigq);
-        f32x4 dKt = zero4(), dQt = zero4(), dKi = zero4(), dA = zero4(), dP = zero4();
-        float dgs = 0.0f;   // sum_v dS'[v][j] S[v][j] for j = 16 w + c (partial over this lane's v)
-        // one pass over the value axis (32 values per step): every operand tile
-        // is read from LDS once
-        // S, dS' rows 32 kp + 4 g + c / 4 (+ 16): the swizzle term is that of
-        // row 4 g + c / 4 for every kp
-        const int sxo = SXH ? sx_lane_offset(16 * w, g, c) : 0;
-#define CARVE_LDSX(B_, R0_) ld_sx_tile<SXH, T, LDSX>(B_, R0_, sxo, 16 * w, g, c)
-        for (int kp = 0; kp < NJT / 2; ++kp) {
-          CARVE_SEQ();
-          const quad s0 = CARVE_LDSX(sSx, 32 * kp);
-          const quad s1 = CARVE_LDSX(sSx, 32 * kp + 16);
-          const quad a0 = CARVE_LDSX(sdSx, 32 * kp);
-          const quad a1 = CARVE_LDSX(sdSx, 32 * kp + 16);
-          const quad r0 = CARVE_LDTR(sdRT, LDX, 32 * kp, 0), r1 = CARVE_LDTR(sdRT, LDX, 32 * kp + 16, 0);
-          const quad o0 = CARVE_LDTR(sdOT, LDX, 32 * kp, 0), o1 = CARVE_LDTR(sdOT, LDX, 32 * kp + 16, 0);
-          const quad u0 = CARVE_LDTR(suT, LDX, 32 * kp, 0), u1 = CARVE_LDTR(suT, LDX, 32 * kp + 16, 0);
-          dKt = Qd::mma32(s0, s1, r0, r1, dKt);
-          dQt = Qd::mma32(s0, s1, o0, o1, dQt);
-          dKi = Qd::mma32(a0, a1, u0, u1, dKi);
-          dA = Qd::mma32(r0, r1, u0, u1, dA);
-          dP = Qd::mma32(o0, o1, u0, u1, dP);
-          // (on the VALU: one more accumulating product here costs the gated
-          // kernels registers they do not have)
-          const f32x4 x0 = Qd::f32(a0), x1 = Qd::f32(a1), y0 = Qd::f32(s0), y1 = Qd::f32(s1);
-          for (int e = 0; e < 4; ++e) dgs += x0[e] * y0[e] + x1[e] * y1[e];
+    // ---- B2: products over the value axis (key tile w; rows j = 16 w + 4 g + i, column t)
+    fresh();
+    // E and the erase gate for the next step
+    f32x4 E[NB];
+    quad sig[NB];
+    for (int tt = 0; tt < NB; ++tt) {
+      E[tt] = rc.template ld<f32x4>(cr.E + (tile0 + tt) * NT * 16, tid * 16);
+      sig[tt] = rc.template ld<quad>(cr.Sig + (tile0 + tt) * NT * QB, tid * QB);
+    }
+    // dA = -dR u^T (s < t) and dP = dO u^T (s <= t), stored as rows of t
+#pragma unroll 1
+    for (int x = w; x < 2 * NTP; x += NW) {
+      const bool isP = x >= NTP;
+      int i = 0, j = isP ? x - NTP : x;
+      while (j >= i + 1) {
+        j -= i + 1;
+        ++i;
+      }
+      const T* b = isP ? sdO : sR;
+      f32x4 acc = zero4();
+      for (int vp = 0; vp < NJT / 2; ++vp)
+        acc = Qd::mma32(Qd::ld(sU + RT::at(16 * j + c, 32 * vp, 4 * g)), Qd::ld(sU + RT::at(16 * j + c, 32 * vp + 16, 4 * g)),
+                        Qd::ld(b + RT::at(16 * i + c, 32 * vp, 4 * g)), Qd::ld(b + RT::at(16 * i + c, 32 * vp + 16, 4 * g)), acc);
+      for (int e = 0; e < 4; ++e) acc[e] = (i > j || 4 * g + e < c + (isP ? 1 : 0)) ? acc[e] : 0.0f;
+      Qd::st(sC + x * ST::N + ST::at(c, 4 * g), Qd::cvt(acc));
+    }
+    f32x4 y[NB], dQ[NB], dKi[NB];
+    float dgs = 0.0f;   // sum_v dM[v][j] S'[v][j] for j = 16 w + c
+    for (int tt = 0; tt < NB; ++tt) {
+      y[tt] = zero4();
+      dQ[tt] = zero4();
+      dKi[tt] = zero4();
+    }
+    for (int vp = 0; vp < NJT / 2; ++vp) {
+      CARVE_SEQ();
+      const quad a0 = RT::tr(sdM, 32 * vp, 16 * w, g, c), a1 = RT::tr(sdM, 32 * vp + 16, 16 * w, g, c);
+      const quad s0 = sS[2 * vp], s1 = sS[2 * vp + 1];
+      for (int tt = 0; tt < NB; ++tt) {
+        const int o0 = RT::at(16 * tt + c, 32 * vp, 4 * g), o1 = RT::at(16 * tt + c, 32 * vp + 16, 4 * g);
+        y[tt] = Qd::mma32(s0, s1, Qd::ld(sR + o0), Qd::ld(sR + o1), y[tt]);
+        dQ[tt] = Qd::mma32(s0, s1, Qd::ld(sdO + o0), Qd::ld(sdO + o1), dQ[tt]);
+        dKi[tt] = Qd::mma32(a0, a1, Qd::ld(sU + o0), Qd::ld(sU + o1), dKi[tt]);
+      }
+      const f32x4 x0 = Qd::f32(a0), x1 = Qd::f32(a1), y0 = Qd::f32(s0), y1 = Qd::f32(s1);
+      for (int e = 0; e < 4; ++e) dgs += x0[e] * y0[e] + x1[e] * y1[e];
+    }
+    dgs += __shfl_xor(dgs, 16);
+    dgs += __shfl_xor(dgs, 32);
+    // wave 0 waits for the next chunk's record; every wave reads the outcome
+    // from LDS after the barrier
+    if (wait_ch >= 0 && w == 0) wait_ready(wait_ch, timed_out);
+    __syncthreads();
+
+    // ---- B3: pair terms, gate gradients ------------------------------------------
+    fresh();
+    // gradients of the token rows go to LDS first (dv, dk over dO and U, dz_w,
+    // dz_b and later dq over dM and R) and out in whole rows from there: stores
+    // of 16 rows for 32 bytes each held up every wave behind the CU's memory
+    // pipeline
+    for (int tt = 0; tt < NB; ++tt) {
+      Qd::st(sdO + RT::at(16 * tt + c, 16 * w, 4 * g), dvT[tt]);
+      if constexpr (!SW) Qd::st(sdM + RT::at(16 * tt + c, 16 * w, 4 * g), dzwT[tt]);
+    }
+    if (wait_ch >= 0) after_wait(s, timed_out);
+    const int nctl = reinterpret_cast<const int*>(smem + lay.Ctl)[0];   // wide bits of the awaited chunk, or -1
+    // the next block, if it can be prefetched: (ch, nx_m) or, at the chunk's
+    // last block, the last block of chunk ch - 1
+    int nch_ = -1, nm_ = nx_m;
+    if (nx_ch_same) nch_ = ch;
+    else if (wait_ch >= 0) {
+      nch_ = wait_ch;
+      nm_ = mpc - 1;
+      if (nctl >= 0 && ((nctl >> nm_) & 1)) nch_ = -1;
+    }
+    // (a block that is not prefetched: its caller loads it; this one's data is
+    // read again then, so that p is written on every path)
+    const int pch = nch_ >= 0 ? nch_ : ch, pm = nch_ >= 0 ? nm_ : tile0 / NBK;
+    // operands of B4 and B5, loaded ahead of this step's stores (a wait for a
+    // load also waits for every store issued before it)
+    quad qT[NB];
+    for (int tt = 0; tt < NB; ++tt)
+      qT[tt] = rc.template ld<quad>(cr.Q + (tile0 + tt) * NT * QB, tid * QB);
+    quad tauq[NVS][(NB + NTW - 1) / NTW], fV[NVS][NJT];
+    for (int k = 0; k < NVS; ++k)
+      for (int jt = 0; jt < NJT; ++jt) fV[k][jt] = Qd::ld(opnd + ((size_t)(k * NJT + jt) * NT + tid) * 4);
+    for (int k = 0; k < NVS; ++k)
+      for (int u = 0; u < (NB + NTW - 1) / NTW; ++u) {
+        const int rt = w % NRW + k * NRW, tt = w / NRW + u * NTW;
+        if (tt < NB)
+          tauq[k][u] = rc.template ld<quad>(cr.Tau + (16 * (tile0 + tt) * RF + 16 * rt) * (int)sizeof(T), (c * RF + 4 * g) * (int)sizeof(T));
+      }
+    f32x4 km[NB];
+    f32x4 dgg;
+    {
+      f32x4 ds = zero4();
+      for (int tt = 0; tt < NB; ++tt) {
+        km[tt] = Qd::f32(Qd::ld(sKi + RT::at(16 * tt + c, 16 * w, 4 * g)));
+        ds += km[tt] * dKi[tt];
+      }
+      for (int i = 0; i < 4; ++i) dgg[i] = __shfl(dgs, 4 * g + i) + row_bcast15(row_scan(ds[i]));
+    }
+    {
+      quad kiT[NB], ktT[NB], qtT[NB];
+      for (int tt = 0; tt < NB; ++tt) {
+        kiT[tt] = RT::tr(sKi, 16 * tt, 16 * w, g, c);
+        ktT[tt] = RT::tr(sKt, 16 * tt, 16 * w, g, c);
+        qtT[tt] = RT::tr(sQt, 16 * tt, 16 * w, g, c);
+      }
+      for (int i = 0; i < NB; ++i)
+        for (int j = 0; j <= i; ++j) {
+          const T* ta = sC + tri_incl(i, j) * ST::N;
+          const T* tp = sC + (NTP + tri_incl(i, j)) * ST::N;
+          y[i] = Qd::mma16(kiT[j], Qd::ld(ta + ST::at(c, 4 * g)), y[i]);
+          dQ[i] = Qd::mma16(kiT[j], Qd::ld(tp + ST::at(c, 4 * g)), dQ[i]);
+          dKi[j] = Qd::mma32(ktT[i], qtT[i], ST::tr(ta, g, c), ST::tr(tp, g, c), dKi[j]);
         }
-        // the transposed operand tiles of the products after the elementwise
-        // gradients, read now: their LDS latency overlaps the permutes below
-        const quad KiT = CARVE_LDTR(sKi, LDK, 0, 16 * w);
-        const quad KtT = CARVE_LDTR(sKt, LDK, 0, 16 * w), QtT = CARVE_LDTR(sQt, LDK, 0, 16 * w);
-        dgs += __shfl_xor(dgs, 16);
-        dgs += __shfl_xor(dgs, 32);
-        const float bc_ = sBeta[c];
-        const f32x4 bq = *reinterpret_cast<const f32x4*>(sBeta + 4 * g);
-        const f32x4 gmj = *reinterpret_cast<const f32x4*>(sGam + 16 * w + 4 * g);
-        // The factors Kt, Qt, Ki that multiply their gradients in dlam (and Ki in
-        // dgam) are the token-dtype values of the operand tiles, exactly as the
-        // products above consumed them.  The pair terms of A and P (and the u^T Ki
-        // term of the state carry) enter dlam twice with opposite signs and cancel
-        // in the suffix sums; with one factor rounded and the other not, the
-        // rounding residue of those large terms would not cancel (bf16: about 1 %
-        // of dl instead of 0.2 %).
-        const int rok = c * LDK + 16 * w + ((4 * g) ^ CARVE_QX(c));
-        const f32x4 kiM = Qd::f32(Qd::ld(sKi + rok));
-        f32x4 bdA, dgg;
+    }
+    // elementwise, last tile first: lane (g, c) holds j = 16 w + 4 g + i, t = 16 tt + c
+    {
+      f32x4 nxt_in = zero4(), dl_in = zero4();   // from the tile after: y Kh of its first token, its dl
+      for (int tt = NB - 1; tt >= 0; --tt) {
+        const f32x4 ktM = Qd::f32(Qd::ld(sKt + RT::at(16 * tt + c, 16 * w, 4 * g)));
+        const f32x4 qtM = Qd::f32(Qd::ld(sQt + RT::at(16 * tt + c, 16 * w, 4 * g)));
+        const float bt = sBeta[16 * tt + c];
+        const f32x4 sg = Qd::f32(sig[tt]);
+        f32x4 dgv, dzb, dkv;
+        float pb = 0.0f;
         for (int i = 0; i < 4; ++i) {
-          // dgam gam = gam (sum_v dS' S + sum_s Ki_s (dS'^T u_s)), reduced over s = the row
-          const float ds = row_scan(kiM[i] * dKi[i]);
-          dgg[i] = gmj[i] * (__shfl(dgs, 4 * g + i) + row_bcast15(ds));
-          dKt[i] = -bc_ * dKt[i];
-          dKi[i] *= gmj[i];
-          const bool lowA = c < 4 * g + i, lowP = c <= 4 * g + i;
-          dA[i] = lowA ? -dA[i] : 0.0f;
-          dP[i] = lowP ? dP[i] : 0.0f;
-          bdA[i] = bq[i] * dA[i];
-        }
-        // beta gradient: A part (dA . A0 summed over s) plus the value partials
-        if (w == 0) {
-          f32x4 A0 = zero4();
-          const T* kr = sKt + c * LDK + ((4 * g) ^ CARVE_QX(c));
-          const T* kir = sKi + c * LDK + ((4 * g) ^ CARVE_QX(c));
-          for (int jp = 0; jp < NJT / 2; ++jp)
-            A0 = Qd::mma32(Qd::ld(kr + 32 * jp), Qd::ld(kr + 32 * jp + 16), Qd::ld(kir + 32 * jp),
-                           Qd::ld(kir + 32 * jp + 16), A0);
-          // (A0 over the whole tile: its entries above the diagonal are products of
-          // factors that may not exist in f32, so they are selected away, not
-          // multiplied by the zeros of dA there)
-          f32x4 db;
-          for (int i = 0; i < 4; ++i) db[i] = row_scan(c < 4 * g + i ? dA[i] * A0[i] : 0.0f);
-          // (summed with the value partials by the last wave in the dtau step)
-          if (c == 15) *reinterpret_cast<f32x4*>(sDbeta + NW * 16 + 4 * g) = db;
-        }
-        const quad bdAT = Qd::cvt(Qd::mma16(Qd::cvt(bdA), CARVE_FI(), zero4()));   // rows s, columns t
-        const quad dPT = Qd::cvt(Qd::mma16(Qd::cvt(dP), CARVE_FI(), zero4()));
-        dKt = Qd::mma16(KiT, bdAT, dKt);
-        dKi = Qd::mma32(KtT, QtT, Qd::cvt(bdA), Qd::cvt(dP), dKi);
-        dQt = Qd::mma16(KiT, dPT, dQt);
-        // elementwise: lane (g, c) holds j = 16 w + 4 g + i, t = c
-        f32x4 dzb, dgv, dkv;
-        {
-        const f32x4 ktM = Qd::f32(Qd::ld(sKt + rok)), qtM = Qd::f32(Qd::ld(sQt + rok));
-        for (int i = 0; i < 4; ++i) {
-          const float Ep = row_shr1(E[i], row_bcast15(Ei[i]));
-          const float nxt = row_shl1(dKt[i] * ktM[i], 0.0f);
-          float dlam = dQt[i] * qtM[i] - dKi[i] * kiM[i] + nxt;
-          if (c == 15) dlam += dgg[i];
-          const float dl = row_suffix(dlam);
+          const float Ei = fast_rcp(E[tt][i]);
+          // e^{lam_{t-1} - rho}; before the block's first token e^{-rho} = 1 / E of the last
+          const float fill = tt > 0 ? row_bcast15(E[tt > 0 ? tt - 1 : 0][i]) : fast_rcp(row_bcast15(E[NB - 1][i]));
+          const float Ep = row_shr1(E[tt][i], fill);
+          const float yk = y[tt][i] * ktM[i];
+          float dlam = dQ[tt][i] * qtM[i] - dKi[tt][i] * km[tt][i] + row_shl1(yk, nxt_in[i]);
+          nxt_in[i] = row_bcast0(yk);
+          if (tt == NB - 1 && c == 15) dlam += dgg[i];
+          const float dl = row_suffix(dlam) + dl_in[i];
+          dl_in[i] = row_bcast0(dl);
           dgv[i] = dl;
-          dzb[i] = -dl * sig[i];
-          dkv[i] = dKt[i] * Ep + dKi[i] * Ei[i];
-          dqp[i] = dQt[i] * E[i];
+          dzb[i] = -dl * sg[i];
+          const float yp = y[tt][i] * Ep;
+          pb += km[tt][i] * E[tt][i] * yp;
+          dkv[i] = bt * yp + dKi[tt][i] * Ei;
+          dQ[tt][i] *= E[tt][i];
         }
-        }
-        Qd::st(dk + e0, Qd::cvt(dkv));
+        Qd::st(sU + RT::at(16 * tt + c, 16 * w, 4 * g), Qd::cvt(dkv));
         if constexpr (GATED) {
           // through Eq. decay_gate: df = dg (-exp(A)) sigmoid(f + tau_f); dA and
-          // dtau collect dg g and df.  f is read again from its staged tile
-          // (the exchange tiles end before it), not kept in registers
-          const int byf = (16 * w + 4 * g) * (int)sizeof(T);
-          const f32x4 fv = Qd::f32(Qd::ld(sFs + c * D + (((((byf >> 4) ^ (c & (NC - 1))) << 4) | (byf & 15)) / (int)sizeof(T))));
-          const f32x4 na = *reinterpret_cast<const f32x4*>(sGate + 16 * w + 4 * g);
-          const f32x4 tf = *reinterpret_cast<const f32x4*>(sGate + D + 16 * w + 4 * g);
+          // dtau collect dg g and df
+          const f32x4 fv = Qd::f32(Qd::ld(reinterpret_cast<const T*>(a.f) + bh0 + e0(tt)));
+          const f32x4 na = *reinterpret_cast<const f32x4*>(gate(0)), tf = *reinterpret_cast<const f32x4*>(gate(1));
           f32x4 dfv;
           for (int i = 0; i < 4; ++i) {
-            float sp, sg;
-            softplus_sigmoid(fv[i] + tf[i], sp, sg);
-            dfv[i] = dgv[i] * na[i] * sg;
-            gaccA[i] += dgv[i] * na[i] * sp;
-            gaccT[i] += dfv[i];
+            float sp, sgf;
+            softplus_sigmoid(fv[i] + tf[i], sp, sgf);
+            dfv[i] = dgv[i] * na[i] * sgf;
+            s.gA[i] += dgv[i] * na[i] * sp;
+            s.gT[i] += dfv[i];
           }
-          Qd::st(dfo + e0, Qd::cvt(dfv));
+          Qd::st(reinterpret_cast<T*>(a.df) + bh0 + e0(tt), Qd::cvt(dfv));
         } else {
-          *reinterpret_cast<f32x4*>(dgo + e0) = dgv;
+          *reinterpret_cast<f32x4*>(a.dg + bh0 + e0(tt)) = dgv;
         }
-        const quad dzbq = Qd::cvt(dzb);
-        Qd::st(dbx + e0, dzbq);
-        Qd::st(sdzb + c * LDD + 16 * w + 4 * g, dzbq);
+        Qd::st(sR + RT::at(16 * tt + c, 16 * w, 4 * g), Qd::cvt(dzb));
+        // dbeta, key part: sum over j of Kt y with Kt = k e^{lam_{t-1} - rho}, k = Ki E
+        pb += __shfl_xor(pb, 16);
+        pb += __shfl_xor(pb, 32);
+        if (g == 0) sDbeta[16 * tt + c] += pb;
       }
-      __syncthreads();
+    }
+    __syncthreads();
 
-      // -- BT: dtau^T (rows r, column t = c) and dY = dtau (1 - tau^2) -> sdY[t][r]
-      for (int x = w; x < (SW ? 1 : 2) * NRB; x += NW) {
-        const int rt = x % NRB, side = x / NRB;
-        f32x4 acc = zero4();
-        if (side == 0) {
-          const T* ar = sVbT + (16 * rt + c) * LDK + ((4 * g) ^ CARVE_QX(c));
-          const T* br = sdzb + c * LDD + 4 * g;
+    // ---- B4: dtau^T (rows r, column t) and dY = dtau (1 - tau^2) -> sdY[t][r] -------
+    fresh();
+    // operands of B5 and of the glue, ahead of the next block's data
+    quad FT[NRT];
+    for (int rt = 0; rt < NRT; ++rt) fU[rt] = Qd::ld(opnd + ((size_t)(NVS * NJT + rt) * NT + tid) * 4);
+    for (int rt = 0; rt < NRT; ++rt) FT[rt] = rc.template ld<quad>(cr.FT + rt * NT * QB, tid * QB);
+    for (int k = 0; k < NVS; ++k)
+      for (int u = 0; u < (NB + NTW - 1) / NTW; ++u) {
+        const int rt = w % NRW + k * NRW, tt = w / NRW + u * NTW;
+        if (tt < NB) {
+          const T* src = rt < NRB ? sR : sdM;   // dz_b or dz_w
+          f32x4 acc = zero4();
           for (int jp = 0; jp < NJT / 2; ++jp)
-            acc = Qd::mma32(Qd::ld(ar + 32 * jp), Qd::ld(ar + 32 * jp + 16), Qd::ld(br + 32 * jp),
-                            Qd::ld(br + 32 * jp + 16), acc);
-        } else {
-          const T* ar = sVwT + (16 * rt + c) * LDK + ((4 * g) ^ CARVE_QX(c));
-          for (int vp = 0; vp < NJT / 2; ++vp)
-            acc = Qd::mma32(Qd::ld(ar + 32 * vp), Qd::ld(ar + 32 * vp + 16), CARVE_LDTR(sdzwT, LDX, 32 * vp, 0),
-                            CARVE_LDTR(sdzwT, LDX, 32 * vp + 16, 0), acc);
+            acc = Qd::mma32(fV[k][2 * jp], fV[k][2 * jp + 1], Qd::ld(src + RT::at(16 * tt + c, 32 * jp, 4 * g)),
+                            Qd::ld(src + RT::at(16 * tt + c, 32 * jp + 16, 4 * g)), acc);
+          const f32x4 tau = Qd::f32(tauq[k][u]);
+          for (int i = 0; i < 4; ++i) acc[i] *= 1.0f - tau[i] * tau[i];
+          Qd::st(sdY + RY::at(16 * tt + c, 16 * rt, 4 * g), Qd::cvt(acc));
         }
-        const int ro = side * RP + 16 * rt + 4 * g;
-        const f32x4 tau = Qd::f32(Qd::ld(sTau + c * LDR + ro));
-        for (int i = 0; i < 4; ++i) acc[i] *= 1.0f - tau[i] * tau[i];
-        Qd::st(sdY + c * LDR + ro, Qd::cvt(acc));
       }
-      // beta gradient: the A part plus the value partials, in that order; and
-      // (scalar write gate) the write-logit gradient from its value partials.
-      // The last wave has no dtau tile at d = 128.
-      if (w == NW - 1 && c == 15) {
-        f32x4 db = *reinterpret_cast<const f32x4*>(sDbeta + NW * 16 + 4 * g);
-        for (int ww = 0; ww < NW; ++ww) {
-          const f32x4 pv = *reinterpret_cast<const f32x4*>(sDbeta + ww * 16 + 4 * g);
-          for (int i = 0; i < 4; ++i) db[i] += pv[i];
-        }
-        for (int i = 0; i < 4; ++i) dbeta[(tb + 4 * g + i) * H] = (T)db[i];
+    store_rows<NB>(a.dv, sdO, t0);
+    store_rows<NB>(a.dk, sU, t0);
+    store_rows<NB>(a.dbx, sR, t0);
+    if constexpr (!SW) store_rows<NB>(a.dwx, sdM, t0);
+    // the next block's data, on its way during B5 and the glue
+    if constexpr (NB == NBK) {
+      load_tiles(p, pch, pm);
+      load_scalars(p, pch, pm);
+      load_uo(p, pch, pm);
+    }
+    // dbeta (and the scalar write gate's dwx): the waves' partials in order
+    if (w == NW - 1)
+      for (int t = tid & 63; t < W; t += 64) {
+        float sb = 0.0f, sw = 0.0f;
+        for (int ww = 0; ww < NW; ++ww) sb += ldf(lay.Dbeta)[ww * W + t];
+        reinterpret_cast<T*>(a.dbeta)[bh1 + (size_t)(t0 + t) * H] = (T)sb;
         if constexpr (SW) {
-          f32x4 dw = zero4();
-          for (int ww = 0; ww < NW; ++ww) {
-            const f32x4 pv = *reinterpret_cast<const f32x4*>(sDwx + ww * 16 + 4 * g);
-            for (int i = 0; i < 4; ++i) dw[i] += pv[i];
-          }
-          for (int i = 0; i < 4; ++i) dwx[(tb + 4 * g + i) * H] = (T)dw[i];
+          for (int ww = 0; ww < NW; ++ww) sw += ldf(lay.Dwx)[ww * W + t];
+          reinterpret_cast<T*>(a.dwx)[bh1 + (size_t)(t0 + t) * H] = (T)sw;
         }
       }
-      // the value-side step took the state gradient with respect to Sr; with
-      // respect to S it carries the factor e^{rho}: applied here before the
-      // glue, otherwise at the next block's staging
-      if (bc == 0) CARVE_BWD_GAM();
-      __syncthreads();
+    __syncthreads();
 
-      // BQ of this block runs at the top of the next block (or before the glue)
-      pdqp = dqp;
-      pqq = qq;
-      pe0 = e0;
+    // ---- B5: dF += dY^T q, dq = dQt E + dY F (key tile w) ------------------------------
+    fresh();
+    // dF starts from that of the chunk's later blocks, parked in its record
+    for (int rt = 0; rt < NRT; ++rt) dF[rt] = zero4();
+    if (16 * (tile0 + NB) < L) {
+      const float* dFr = reinterpret_cast<const float*>(rec_of(ch) + cr.dF) + (size_t)(16 * w + c) * RF + 4 * g;
+      for (int rt = 0; rt < NRT; ++rt) dF[rt] = *reinterpret_cast<const f32x4*>(dFr + 16 * rt);
+      // (waited for here: a load still pending where the two paths join would
+      // make both of them wait, for the next block's data too)
+      for (int rt = 0; rt < NRT; ++rt) arrived(dF[rt]);
     }
-    if (bc != 0) continue;
-    {
-    // opaque lane coordinates for the glue as well (its LDS addresses are
-    // recomputed here rather than held across the loop)
-    int tid_ = tid, g_ = g, c_ = c, w_ = w;
-    asm volatile("" : "+v"(tid_), "+v"(g_), "+v"(c_), "+v"(w_));
-    const int tid = tid_, g = g_, c = c_, w = w_;
-    (void)tid;
-    CARVE_BWD_BQ();
-
-    // ---- glue: dS += [Ub; Uw]^T dF; dF is parked in the chunk record for
-    // d[Ub; Uw] += dF S_hat^T (carve_bwd_param_kernel).  dF enters the product
-    // as a high and a low part so that its f32 accumulation is not rounded away.
-    {
-      constexpr int LDF = R2 + 4;   // row stride of the dF parts (LDS layout)
-      T* sdFh = sdSx;               // [D][LDF]: dF[r][j] stored at (j, r)
-      T* sdFl = sdSx + D * LDF;     // [D][LDF]: dF - (dF rounded)
-      float* dFr = reinterpret_cast<float*>(const_cast<char*>(rc) + cr.dF);
-      __syncthreads();  // every wave is done with sdSx and sdY of the last block
-      for (int rt = 0; rt < NRT; ++rt) {
-        const quad hi = Qd::cvt(dF[rt]);
-        Qd::st(sdFh + (16 * w + c) * LDF + 16 * rt + 4 * g, hi);
-        Qd::st(sdFl + (16 * w + c) * LDF + 16 * rt + 4 * g, Qd::cvt(dF[rt] - Qd::f32(hi)));
-        // dF parked as [j][r] (a lane holds four consecutive r of one j: one
-        // 16-byte store per tile); the d[Ub; Uw] kernel transposes it in LDS
-        *reinterpret_cast<f32x4*>(dFr + (size_t)(16 * w + c) * R2 + 16 * rt + 4 * g) = dF[rt];
-        dF[rt] = zero4();
+    for (int rt = 0; rt < NRT; ++rt) arrived(fU[rt]);
+    for (int rt = 0; rt < NRT; ++rt) {
+      if constexpr (NB == 1) {
+        dF[rt] = Qd::mma16(RY::tr(sdY, 0, 16 * rt, g, c), qT[0], dF[rt]);
+      } else {
+        for (int tp = 0; tp < NB / 2; ++tp)
+          dF[rt] = Qd::mma32(RY::tr(sdY, 32 * tp, 16 * rt, g, c), RY::tr(sdY, 32 * tp + 16, 16 * rt, g, c), qT[2 * tp],
+                               qT[2 * tp + 1], dF[rt]);
       }
-      __syncthreads();
+    }
+    for (int tt = 0; tt < NB; ++tt) {
+      f32x4 acc = dQ[tt];
+      for (int rp = 0; rp < NRT / 2; ++rp)
+        acc = Qd::mma32(FT[2 * rp], FT[2 * rp + 1], Qd::ld(sdY + RY::at(16 * tt + c, 32 * rp, 4 * g)),
+                        Qd::ld(sdY + RY::at(16 * tt + c, 32 * rp + 16, 4 * g)), acc);
+      Qd::st(sR + RT::at(16 * tt + c, 16 * w, 4 * g), Qd::cvt(acc));
+    }
+    for (int rt = 0; rt < NRT; ++rt) arrived(dF[rt]);
+    if (tile0 > 0) park_dF(dF, ch);
+  }
+  // NB * 16 token rows of a tile to the rows from t0 on of a token tensor
+  template <int NB>
+  __device__ __forceinline__ void store_rows(void* dst, const T* tile, int t0) const {
+    T* d = reinterpret_cast<T*>(dst) + bh0 + (size_t)t0 * rs;
+    constexpr int N = 16 * NB * D / VEC;
+    for (int u = 0; u < (N + NT - 1) / NT; ++u) {
+      const int x = tid + u * NT;
+      if (N % NT != 0 && x >= N) break;
+      const int row = x / (D / VEC), k = x % (D / VEC);
+      *reinterpret_cast<u32x4_t*>(d + row * rs + k * VEC) = unstage_vec<T, D>(tile, row, k);
+    }
+  }
+  // dF of a chunk in its record, as [j][r] (a lane holds four consecutive r of
+  // one j: one 16-byte store per tile)
+  __device__ __forceinline__ void park_dF(const f32x4 (&dF)[NRT], int ch) const {
+    float* dFr = reinterpret_cast<float*>(const_cast<char*>(rec_of(ch)) + cr.dF) + (size_t)(16 * w + c) * RF + 4 * g;
+    for (int rt = 0; rt < NRT; ++rt) *reinterpret_cast<f32x4*>(dFr + 16 * rt) = dF[rt];
+  }
+
+  // wave 0: wait until chunk need's flag is raised (the record is read with
+  // agent-scope loads, RecBuf, so no cache is invalidated here); Ctl[0] = its wide bits, or
+  // -1 if the bound ran out (or had before)
+  __device__ __forceinline__ void wait_ready(int need, bool timed_out) const {
+    int* ctl = reinterpret_cast<int*>(smem + lay.Ctl);
+    const int* rdy = ready + (size_t)bh * nch + need;
+    int v = 0;
+    if (!timed_out)
+      for (int n = 0; n < a.wait_limit; ++n) {
+        v = __hip_atomic_load(rdy, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (v != 0) break;
+        __builtin_amdgcn_s_sleep(2);
+      }
+    if (lane == 0) ctl[0] = v != 0 ? v >> 1 : -1;
+  }
+  // every wave, after the barrier that follows wait_ready
+  __device__ __forceinline__ void after_wait(State& s, bool& timed_out) const {
+    const int v = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(smem + lay.Ctl)[0]);
+    if (v < 0 && !timed_out) {
+      timed_out = true;
+      const float n = __builtin_nanf("");
+      for (int jt = 0; jt < NJT; ++jt) s.dS[jt] = f32x4{n, n, n, n};
+      if (tid == 0) __hip_atomic_store(timeout_word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+
+  const int* ready;
+  int* timeout_word;
+  int* pos;
+
+  // dS += [Ub; Uw]^T dF at a chunk start; dF is parked in the chunk record for
+  // d[Ub; Uw] += dF S_hat^T (carve_bwd_param_kernel).  dF enters the product as
+  // a high and a low part (bf16) so that its f32 accumulation is not rounded
+  // away.  Reads dY's step as finished only after its barrier.
+  __device__ __forceinline__ void glue(State& s, f32x4 (&dF)[NRT], const quad (&fU)[NRT], int ch) {
+    fresh();
+    T* sh = lds(lay.U);
+    T* sl = sh + D * LDF;
+    for (int rt = 0; rt < NRT; ++rt) {
+      const quad hi = Qd::cvt(dF[rt]);
+      Qd::st(sh + df_at(16 * w + c, 16 * rt + 4 * g), hi);
+      if constexpr (SPLIT) Qd::st(sl + df_at(16 * w + c, 16 * rt + 4 * g), Qd::cvt(dF[rt] - Qd::f32(hi)));
+    }
+    park_dF(dF, ch);
+    __syncthreads();
+    for (int jt = 0; jt < NJT; ++jt) {
+      CARVE_SEQ();
+      f32x4 acc = s.dS[jt];
+      for (int rp = 0; rp < NRT / 2; ++rp) {
+        const int o0 = df_at(16 * jt + c, 32 * rp + 4 * g), o1 = df_at(16 * jt + c, 32 * rp + 16 + 4 * g);
+        acc = Qd::mma32(Qd::ld(sh + o0), Qd::ld(sh + o1), fU[2 * rp], fU[2 * rp + 1], acc);
+        if constexpr (SPLIT) acc = Qd::mma32(Qd::ld(sl + o0), Qd::ld(sl + o1), fU[2 * rp], fU[2 * rp + 1], acc);
+      }
+      s.dS[jt] = acc;
+    }
+  }
+
+  __device__ __forceinline__ void run() {
+    // operand quads of the parameters, written once to this workgroup's part of
+    // the workspace in thread order and read back where they are used (each
+    // thread its own; from cache): V^T of the wave's dtau tiles (lane (g, c):
+    // V[16 jt + 4 g + e][16 rt' + c], rows past R zero) and [Ub; Uw] of the glue
+    // (lane (g, c): U[16 rt + 4 g + e][16 w + c]).  Held in registers they would
+    // push the block's tiles into scratch.
+    for (int k = 0; k < NVS; ++k) {
+      const int rt = w % NRW + k * NRW;
+      const float* src = rt < NRB ? a.Vb : a.Vw;
+      const int r = 16 * (rt % NRB) + c;
       for (int jt = 0; jt < NJT; ++jt) {
-        CARVE_SEQ();
-        // the tile's dF parts in one batch of LDS reads ahead of its products
-        quad fh[R2 / 16], fl[R2 / 16];
-        for (int rq = 0; rq < R2 / 16; ++rq) {
-          const int o = (16 * jt + c) * LDF + 16 * rq + 4 * g;
-          fh[rq] = Qd::ld(sdFh + o);
-          fl[rq] = Qd::ld(sdFl + o);
-        }
-        if constexpr (R2 == 64)
-          asm volatile("" : "+v"(fh[0]), "+v"(fh[1]), "+v"(fh[2]), "+v"(fh[3]), "+v"(fl[0]), "+v"(fl[1]), "+v"(fl[2]), "+v"(fl[3]));
-        f32x4 acc = dSt[jt];
-        for (int rp = 0; rp < R2 / 32; ++rp) {
-          acc = Qd::mma32(fh[2 * rp], fh[2 * rp + 1], fU[2 * rp], fU[2 * rp + 1], acc);
-          acc = Qd::mma32(fl[2 * rp], fl[2 * rp + 1], fU[2 * rp], fU[2 * rp + 1], acc);
-        }
-        dSt[jt] = acc;
+        f32x4 t;
+        for (int e = 0; e < 4; ++e) t[e] = r < R ? src[(16 * jt + 4 * g + e) * R + r] : 0.0f;
+        Qd::st(opnd + ((size_t)(k * NJT + jt) * NT + tid) * 4, Qd::cvt(t));
       }
-      // (no barrier: the next block writes sdSx only after its first barrier,
-      // and what it stages before that barrier does not overlap the dF parts)
     }
+    for (int rt = 0; rt < NRT; ++rt) {
+      const float* src = rt < NRB ? a.Ub : a.Uw;
+      f32x4 t;
+      for (int e = 0; e < 4; ++e) {
+        const int r = 16 * (rt % NRB) + 4 * g + e;
+        t[e] = r < R ? src[r * D + 16 * w + c] : 0.0f;
+      }
+      Qd::st(opnd + ((size_t)(NVS * NJT + rt) * NT + tid) * 4, Qd::cvt(t));
     }
-  }  // blocks (reverse)
+    if constexpr (GATED)
+      for (int e = 0; e < 4; ++e) {
+        gate(0)[e] = -expf(a.A[h * D + 16 * w + 4 * g + e]);
+        gate(1)[e] = a.tau_f[h * D + 16 * w + 4 * g + e];
+      }
+    State s;
+    const size_t soff = (size_t)bh * D * D;
+    for (int jt = 0; jt < NJT; ++jt)
+      s.dS[jt] = a.dS_T ? gload4(a.dS_T + soff + (16 * w + c) * D + 16 * jt + 4 * g) : zero4();
+    s.gA = s.gT = zero4();
+    Pre p;
+    bool timed_out = false;
+    int dq_t0 = -1;         // first token of the block whose dq rows are in LDS
+    bool in_regs = false;   // the next block's data is (on its way) in p
+    if (w == 0) wait_ready(nch - 1, false);
+    __syncthreads();
+    after_wait(s, timed_out);
 
-#undef CARVE_BWD_BQ
-#undef CARVE_BWD_GAM
-#undef CARVE_QX
-#undef CARVE_LDTR
-#undef CARVE_LDSX
-#undef CARVE_BWD_READY
-#undef CARVE_BWD_LOADA
-#undef CARVE_BWD_LOADS
-#undef CARVE_BWD_LOADF
-  if constexpr (GATED) {
-    // the lanes' sums over their tokens, reduced over the 16 lanes of a row
-    // (all tokens of a block) and written by lane c = 0, one owner per channel
-    for (int i = 0; i < 4; ++i) {
-      gaccA[i] = row_suffix(gaccA[i]);
-      gaccT[i] = row_suffix(gaccT[i]);
+#pragma unroll 1
+    for (int ch = nch - 1; ch >= 0; --ch) {
+      const int ctl = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(smem + lay.Ctl)[0]);
+      const int wide = ctl > 0 ? ctl : 0;
+      if (tid == 0) __hip_atomic_store(pos, nch - ch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      f32x4 dF[NRT];
+      quad fU[NRT];
+#pragma unroll 1
+      for (int m = mpc - 1; m >= 0; --m) {
+        const int wait_ch = m == 0 ? ch - 1 : -1;
+        if (!((wide >> m) & 1)) {
+          if (!in_regs) {
+            load_tiles(p, ch, m);
+            load_scalars(p, ch, m);
+            load_uo(p, ch, m);
+          }
+          load_vals(p, ch, m);   // (first used in the middle of B1)
+          // (the last readers of the other regions were before B5; U and dO are
+          // read by the glue)
+          put_tiles(p);
+          __syncthreads();
+          if (dq_t0 >= 0) store_rows<NBK>(a.dq, lds(lay.R), dq_t0);
+          put_uo(p);
+          __syncthreads();
+          const bool same = m > 0 && !((wide >> (m - 1)) & 1);
+          block<NBK>(s, p, dF, fU, ch, m * NBK, wait_ch, timed_out, same ? 1 : 0, m - 1);
+          dq_t0 = ch * L + m * W;
+          in_regs = same;
+          if (m == 0 && ch > 0) {
+            const int nc = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(smem + lay.Ctl)[0]);
+            in_regs = !(nc > 0 && ((nc >> (mpc - 1)) & 1));
+          }
+          if (m == 0) glue(s, dF, fU, ch);
+        } else if constexpr (NBK > 1) {
+#pragma unroll 1
+          for (int i = NBK - 1; i >= 0; --i) {
+            __syncthreads();
+            if (dq_t0 >= 0) store_rows<NBK>(a.dq, lds(lay.R), dq_t0);
+            dq_t0 = -1;
+            load_tile_direct(p, ch, m, i);
+            __syncthreads();
+            block<1>(s, p, dF, fU, ch, m * NBK + i, i == 0 ? wait_ch : -1, timed_out, 0, 0);
+            __syncthreads();
+            store_rows<1>(a.dq, lds(lay.R), ch * L + m * W + 16 * i);
+          }
+          // nothing of this path is pending where it joins the other one (the
+          // join would wait for the next block's data otherwise)
+          vm_wait_all();
+          in_regs = false;
+          if (m == 0) glue(s, dF, fU, ch);
+        }
+      }
     }
-    if (c == 0) {
-      float* dst = a.partG + (size_t)bh * 2 * D + 16 * w + 4 * g;
-      *reinterpret_cast<f32x4*>(dst) = gaccA;
-      *reinterpret_cast<f32x4*>(dst + D) = gaccT;
+    __syncthreads();
+    if (dq_t0 >= 0) store_rows<NBK>(a.dq, lds(lay.R), dq_t0);
+    if constexpr (GATED) {
+      // the lanes' sums over their tokens, reduced over the 16 lanes of a row
+      // (all tokens of a tile) and written by lane c = 0, one owner per channel
+      for (int i = 0; i < 4; ++i) {
+        s.gA[i] = row_suffix(s.gA[i]);
+        s.gT[i] = row_suffix(s.gT[i]);
+      }
+      if (c == 0) {
+        float* dst = a.partG + (size_t)bh * 2 * D + 16 * w + 4 * g;
+        *reinterpret_cast<f32x4*>(dst) = s.gA;
+        *reinterpret_cast<f32x4*>(dst + D) = s.gT;
+      }
+    }
+    if (a.dS0) {
+      float* dst = a.dS0 + soff + (16 * w + c) * D + 4 * g;
+      for (int jt = 0; jt < NJT; ++jt) *reinterpret_cast<f32x4*>(dst + 16 * jt) = s.dS[jt];
     }
   }
-  if (a.dS0) {
-    float* dst = a.dS0 + soff + (16 * w + c) * D + 4 * g;
-    for (int jt = 0; jt < NJT; ++jt) *reinterpret_cast<f32x4*>(dst + 16 * jt) = dSt[jt];
+
+  __device__ __forceinline__ Adjoint(const BwdArgs& a_, int bh_, char* smem_, const int* ready_, int* timeout_, int* pos_)
+      : a(a_), bh(bh_), smem(smem_), ready(ready_), timeout_word(timeout_), pos(pos_) {
+    tid = threadIdx.x;
+    lane = tid & 63;
+    w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    g = lane >> 4;
+    c = lane & 15;
+    H = a.H;
+    L = a.L;
+    R = a.R;
+    nch = a.T / L;
+    mpc = L / W;
+    rs = H * D;
+    h = bh % H;
+    cr = chunk_rec<T, D>(L, RF, NBK);
+    bh0 = ((size_t)(bh / H) * a.T * H + h) * D;
+    bh1 = (size_t)(bh / H) * a.T * H + h;
+    recb = reinterpret_cast<const char*>(a.rec) + (size_t)bh * nch * cr.total;
+    opnd = reinterpret_cast<T*>(reinterpret_cast<char*>(a.opnd) + (size_t)bh * adj_opnd_bytes(D, 2 * RP, sizeof(T)));
   }
-}
+};
 
 // Chunk recompute and adjoint in one grid of nrec + B*H workgroups.  Roles go
 // by arrival: each workgroup draws a ticket from the counter in sync; the first
 // nrec tickets recompute, the rest run the adjoint of (batch, head) ticket -
-// nrec.  A workgroup with a recompute ticket is already running and never
-// waits, so every flag an adjoint workgroup waits for is raised in finite time
-// whatever order the hardware dispatches the grid in.  Recompute items are
-// taken latest chunk first (the order in which the adjoint needs them): item
-// i is chunk nch - 1 - i / (B*H) of (batch, head) i % (B*H).  With lead > 0 a
-// recompute workgroup starts that chunk only once the adjoint of its (batch,
-// head) has started the chunk lead places before it (a bounded wait: the
-// recompute still never waits for long): records are then written shortly
-// before they are read, and the recompute's stores do not all come at once.
-// Measured at the headline shape, a lead of 3-4 chunks takes the fused
-// launch from 2.01 to 1.90 ms; 1 chunk starves the adjoint.
-template <typename T, int D, int LW, int RP, int VAR>
+// nrec.  A workgroup with a recompute ticket is already running and waits only
+// for a bounded time, so every flag an adjoint workgroup waits for is raised in
+// finite time whatever order the hardware dispatches the grid in.  With lead >
+// 0 a recompute workgroup starts a chunk only once the adjoint of its (batch,
+// head) has started the chunk lead places before it (a bounded wait): records
+// are then written shortly before they are read, and the recompute's stores do
+// not all come at once.
+template <typename T, int D, int RP, int VAR, int NB>
 __global__ void __launch_bounds__(bwd_threads(D)) __attribute__((amdgpu_waves_per_eu(1, 2)))
 carve_bwd_fused_kernel(FwdArgs f, BwdArgs a, int nrec, int* sync, int lead) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int nbh = a.B * a.H, nch = a.T / a.L;
-  const int nitems = nbh * nch;
-  int* ready = sync;
   if (threadIdx.x == 0)
     reinterpret_cast<int*>(smem)[0] =
         __hip_atomic_fetch_add(sync + sync_ticket(nbh, nch), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -957,43 +863,24 @@ carve_bwd_fused_kernel(FwdArgs f, BwdArgs a, int nrec, int* sync, int lead) {
   const int ticket = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(smem)[0]);
   __syncthreads();
   if (ticket < nrec) {
-    for (int item = ticket; item < nitems; item += nrec) {
-      const int ch = nch - 1 - item / nbh, bh = item % nbh;
-      const int row = item / nbh;   // chunks after ch
-      if (lead > 0 && row >= lead) {
-        if (threadIdx.x == 0) {
-          const int* p = sync + sync_adjoint_pos(nbh, nch) + bh;
-          for (int n = 0; n < kLeadSpinLimit; ++n) {
-            if (__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > row - lead) break;
-            __builtin_amdgcn_s_sleep(4);
-          }
-        }
-        __syncthreads();
-      }
-      rec_chunk<T, D, LW, RP, VAR>(f, bh, ch, smem);
-      // every wave's record stores are complete before the barrier; the
-      // release store (agent scope) then writes them back for other XCDs
-      vm_wait_all();
-      __syncthreads();
-      if (threadIdx.x == 0)
-        __hip_atomic_store(ready + (size_t)bh * nch + ch, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    rec_run<T, D, RP, VAR, NB>(f, ticket, nrec, sync, lead, kLeadSpinLimit, smem);
   } else {
-    bwd_adjoint<T, D, RP, VAR>(a, ticket - nrec, smem, ready, sync + sync_timeout_word(nbh, nch),
-                               sync + sync_adjoint_pos(nbh, nch) + (ticket - nrec));
+    const int bh = ticket - nrec;
+    Adjoint<T, D, RP, VAR, NB>(a, bh, smem, sync, sync + sync_timeout_word(nbh, nch), sync + sync_adjoint_pos(nbh, nch) + bh)
+        .run();
   }
 }
 
 // ---------------------------------------------------------------------------
 // host-side launch
 // ---------------------------------------------------------------------------
-template <typename T, int D, int LW, int RP, int VAR>
+template <typename T, int D, int RP, int VAR, int NB>
 static int launch_fused_t(const FwdArgs& f, const BwdArgs& a, int* sync, int cus, hipStream_t stream) {
-  constexpr size_t lds = fused_lds<T, D, LW, RP, VAR>();
+  constexpr size_t lds = fused_lds<T, D, RP, VAR, NB>();
   if constexpr (lds > kMaxLdsBytes) {
     return CARVE_ERR_UNSUPPORTED;
   } else {
-    auto kern = carve_bwd_fused_kernel<T, D, LW, RP, VAR>;
+    auto kern = carve_bwd_fused_kernel<T, D, RP, VAR, NB>;
     static bool attr_set = false;  // per instantiation
     if (!attr_set) {
       if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1020,31 +907,35 @@ static int launch_fused_t(const FwdArgs& f, const BwdArgs& a, int* sync, int cus
 }
 
 template <typename T, int D, int RP, int VAR>
-static int launch_fused_l(const FwdArgs& f, const BwdArgs& a, int* sync, int cus, int LW, hipStream_t s) {
-  if (LW == 16) return launch_fused_t<T, D, 16, RP, VAR>(f, a, sync, cus, s);
-  if (LW == 32) return launch_fused_t<T, D, 32, RP, VAR>(f, a, sync, cus, s);
+static int launch_fused_l(const FwdArgs& f, const BwdArgs& a, int* sync, int cus, int NB, hipStream_t s) {
+  if (NB == 1) return launch_fused_t<T, D, RP, VAR, 1>(f, a, sync, cus, s);
+  if constexpr (sizeof(T) == 2) {   // f32: one-tile blocks only (bwd_lds_bytes)
+    if (NB == 2) return launch_fused_t<T, D, RP, VAR, 2>(f, a, sync, cus, s);
+    if (NB == 4) return launch_fused_t<T, D, RP, VAR, 4>(f, a, sync, cus, s);
+  }
   return CARVE_ERR_UNSUPPORTED;
 }
 
 template <typename T, int VAR>
-static int launch_fused_d(const FwdArgs& f, const BwdArgs& a, int* sync, int cus, int D, int LW, hipStream_t s) {
+static int launch_fused_d(const FwdArgs& f, const BwdArgs& a, int* sync, int cus, int D, int NB, hipStream_t s) {
   if (a.RP == 32) {
-    if (D == 32) return launch_fused_l<T, 32, 32, VAR>(f, a, sync, cus, LW, s);
-    if (D == 64) return launch_fused_l<T, 64, 32, VAR>(f, a, sync, cus, LW, s);
-    if (D == 128) return launch_fused_l<T, 128, 32, VAR>(f, a, sync, cus, LW, s);
+    if (D == 32) return launch_fused_l<T, 32, 32, VAR>(f, a, sync, cus, NB, s);
+    if (D == 64) return launch_fused_l<T, 64, 32, VAR>(f, a, sync, cus, NB, s);
+    if constexpr (sizeof(T) == 2)
+      if (D == 128) return launch_fused_l<T, 128, 32, VAR>(f, a, sync, cus, NB, s);
   } else if (a.RP == 64) {
-    if (D == 32) return launch_fused_l<T, 32, 64, VAR>(f, a, sync, cus, LW, s);
-    if (D == 64) return launch_fused_l<T, 64, 64, VAR>(f, a, sync, cus, LW, s);
-    if (D == 128) return launch_fused_l<T, 128, 64, VAR>(f, a, sync, cus, LW, s);
+    if (D == 32) return launch_fused_l<T, 32, 64, VAR>(f, a, sync, cus, NB, s);
+    if constexpr (sizeof(T) == 2)
+      if (D == 64) return launch_fused_l<T, 64, 64, VAR>(f, a, sync, cus, NB, s);
   }
   return CARVE_ERR_UNSUPPORTED;
 }
 
 template <int VAR>
-int launch_bwd_fused_var(const FwdArgs& f, const BwdArgs& a, int* sync, int cus, int dtype, int D, int LW,
+int launch_bwd_fused_var(const FwdArgs& f, const BwdArgs& a, int* sync, int cus, int dtype, int D, int NB,
                          hipStream_t s) {
-  if (dtype == CARVE_BF16) return launch_fused_d<bf16_t, VAR>(f, a, sync, cus, D, LW, s);
-  return launch_fused_d<float, VAR>(f, a, sync, cus, D, LW, s);
+  if (dtype == CARVE_BF16) return launch_fused_d<bf16_t, VAR>(f, a, sync, cus, D, NB, s);
+  return launch_fused_d<float, VAR>(f, a, sync, cus, D, NB, s);
 }
 
 }  // namespace carve

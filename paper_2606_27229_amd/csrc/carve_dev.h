@@ -18,6 +18,9 @@ typedef __bf16 bf16_t;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
 
 namespace carve {
 
@@ -122,9 +125,12 @@ struct Quad<bf16_t> {
   }
   static __device__ __forceinline__ void st(bf16_t* p, q v) { *reinterpret_cast<bf16x4*>(p) = v; }
   static __device__ __forceinline__ q cvt(f32x4 x) {
-    q o;
-    o[0] = (bf16_t)x[0]; o[1] = (bf16_t)x[1]; o[2] = (bf16_t)x[2]; o[3] = (bf16_t)x[3];
-    return o;
+    // by pairs, one conversion instruction each: from a four-element conversion
+    // the compiler converts every value on its own and packs them afterwards
+    const f32x2 a = {x[0], x[1]}, b = {x[2], x[3]};
+    const u32x2_t r = {__builtin_bit_cast(unsigned, __builtin_convertvector(a, bf16x2)),
+                       __builtin_bit_cast(unsigned, __builtin_convertvector(b, bf16x2))};
+    return __builtin_bit_cast(q, r);
   }
   static __device__ __forceinline__ f32x4 f32(q x) {
     f32x4 o = {(float)x[0], (float)x[1], (float)x[2], (float)x[3]};
@@ -135,8 +141,8 @@ struct Quad<bf16_t> {
   }
   // two K16 slices in one K32 step (the same slice pairing on both sides)
   static __device__ __forceinline__ f32x4 mma32(q a0, q a1, q b0, q b1, f32x4 c) {
-    const bf16x8 a = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
-    const bf16x8 b = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3]};
+    const bf16x8 a = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
+    const bf16x8 b = __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7);
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   }
 };
@@ -216,6 +222,38 @@ __device__ __forceinline__ f32x4 gload4(const bf16_t* p) {
 }
 __device__ __forceinline__ f32x4 gload4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 
+// Chunk-record accesses between compute units of different XCDs: buffer
+// operations at agent scope (sc1).  Such a store goes through the XCD's L2 to
+// the coherence point, and such a load comes from there, so that publishing a
+// record needs no write-back of the whole L2 and reading it no invalidation:
+// a wait for the writer's stores and a flag are enough.  The address is a
+// uniform base (the record), a uniform byte offset and a 32-bit lane offset.
+typedef unsigned u32x4_g __attribute__((ext_vector_type(4)));
+struct RecBuf {
+  __amdgpu_buffer_rsrc_t r;
+  __device__ __forceinline__ RecBuf(const void* base, unsigned bytes)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00027000)) {}
+  static constexpr int kAgent = 16;   // sc1
+  template <typename V>
+  __device__ __forceinline__ void st(unsigned off, unsigned lane_off, V v) const {
+    if constexpr (sizeof(V) == 16)
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_g, v), r, (int)lane_off, (int)off, kAgent);
+    else if constexpr (sizeof(V) == 8)
+      __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), r, (int)lane_off, (int)off, kAgent);
+    else
+      __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)lane_off, (int)off, kAgent);
+  }
+  template <typename V>
+  __device__ __forceinline__ V ld(unsigned off, unsigned lane_off) const {
+    if constexpr (sizeof(V) == 16)
+      return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)off, kAgent));
+    else if constexpr (sizeof(V) == 8)
+      return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b64(r, (int)lane_off, (int)off, kAgent));
+    else
+      return __builtin_bit_cast(V, __builtin_amdgcn_raw_buffer_load_b32(r, (int)lane_off, (int)off, kAgent));
+  }
+};
+
 // DPP helpers inside rows of 16 lanes
 // x of the lane one to the left in its row; the first lane of a row gets fill
 __device__ __forceinline__ float row_shr1(float x, float fill) {
@@ -231,6 +269,10 @@ __device__ __forceinline__ float row_shl1(float x, float fill) {
 // no old value is needed)
 __device__ __forceinline__ float row_bcast15(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x15F, 0xf, 0xf, false));
+}
+// x of lane 0 of the row, in every lane of the row
+__device__ __forceinline__ float row_bcast0(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x150, 0xf, 0xf, false));
 }
 // x of the neighbouring lane (lane ^ 1)
 __device__ __forceinline__ float lane_xor1(float x) {

@@ -39,39 +39,99 @@ struct FwdArgs {
   int B, T, H, R, RP, L;
 };
 
-// Per-(batch, head, chunk) record written by the chunk-parallel recompute of
-// the backward and read by its adjoint kernel (byte offsets, 256-aligned); RF
-// is the variant's number of fold rows (fold_rows):
-//   F   [RF][D]    token dtype   folded read-out of the chunk start state
-//   Tau [L][RF]    token dtype   tanh(q F^T)
-//   Tm  [L/16][16][16]           T = (I + A)^{-1} of every 16-token block
-//   P   [L/16][16][16]           P of every block
-//   S   [L/16][D/16][threads][4]  block start states scaled by the block's reference,
-//                                 Sr = S diag(e^{rho}) with rho = lam_15 / 2 per key
-//                                 channel: quad jt of thread tid
-//                                 (Sr[16 w + c][16 jt + 4 g + e]), contiguous over threads
-//   E   [L/16][16][D]  f32       e^{lam_t - rho} of every token and key channel (its
-//                                 block's reference; not written by the GATED kernels)
-//   Sig [L/16][16][D]  token dtype  sigma(z_b) of every token and key channel (the
-//                                 erase gate b; not written by the GATED kernels)
-//   dF  [D][RF]    f32           written by the adjoint: the chunk's gradient of F,
-//                                 stored transposed (dF[r][j] at (j, r))
-struct ChunkRec {
-  size_t F, Tau, Tm, P, S, E, Sig, dF, total;
+// ---- rows of D token-dtype elements as matrix-core operands ---------------------
+// Row stride (elements) and element-index XOR of a [rows][D] operand tile whose
+// quads (4 elements, 8 bytes in bf16) are read along a row (in pairs 16 columns
+// apart, one LDS instruction) and across rows and written as result quads: bf16
+// rows of 16 (mod 32) elements with qswz, f32 rows with a 16-byte pad.
+template <typename T, int D>
+struct RowTile {
+  static constexpr int LD = sizeof(T) == 2 ? (D % 32 == 16 ? D : D + 16) : D + 4;
+  static __device__ __forceinline__ int sw(int r) { return qswz<T>(r); }
+  // element offset of (row r, column c0 + q), c0 a multiple of 16 and q = 0, 4, 8
+  // or 12 (the swizzle moves q only, so offsets along a row stay immediate)
+  static __device__ __forceinline__ int at(int r, int c0, int q) { return r * LD + c0 + (q ^ sw(r)); }
+  // lane (g, c) receives tile[r0 + 4 g + e][c0 + c], e = 0..3 (r0, c0 multiples of 16)
+  static __device__ __forceinline__ typename Quad<T>::q tr(const T* t, int r0, int c0, int g, int c) {
+    return Quad<T>::ld_tr_sw(t, LD, r0, c0, g, c);
+  }
 };
-__host__ __device__ constexpr size_t rec_align(size_t x) { return (x + 255) & ~(size_t)255; }
-__host__ __device__ constexpr ChunkRec chunk_rec(size_t e, int D, int L, int RF) {
+// 16 x 16 coupling tiles (A, P, T, dA, dP), one after another: rows of 16
+// elements with qswz (bf16), or 20 (f32)
+template <typename T>
+struct SmallTile {
+  static constexpr int LD = sizeof(T) == 2 ? 16 : 20;
+  static constexpr int N = 16 * LD;   // elements of a tile
+  static __device__ __forceinline__ int at(int r, int col) { return r * LD + (col ^ qswz<T>(r)); }
+  static __device__ __forceinline__ typename Quad<T>::q tr(const T* t, int g, int c) {
+    return Quad<T>::ld_tr_sw(t, LD, 0, 0, g, c);
+  }
+};
+
+// Lower-triangular 16-token tile pairs (i, j) of a block of NB tiles, row-major:
+// inclusive (j <= i) and strict (j < i) enumeration.
+__host__ __device__ constexpr int tri_incl(int i, int j) { return i * (i + 1) / 2 + j; }
+__host__ __device__ constexpr int tri_strict(int i, int j) { return i * (i - 1) / 2 + j; }
+// coupling tiles of a block: P (inclusive), -A (strict), T (one per tile)
+__host__ __device__ constexpr int tiles_p(int NB) { return NB * (NB + 1) / 2; }
+__host__ __device__ constexpr int tiles_a(int NB) { return NB * (NB - 1) / 2; }
+__host__ __device__ constexpr int tiles_all(int NB) { return tiles_p(NB) + tiles_a(NB) + NB; }
+
+// Per-(batch, head, chunk) record written by the chunk-parallel recompute of
+// the backward and read by its adjoint (byte offsets, 256-aligned).  The chunk
+// is L / (16 NB) WY blocks of NB 16-token tiles; NT threads per workgroup, RF
+// fold rows (fold_rows), thread tid = 64 w + 16 g + c.  "Thread order": the
+// 4-element vector of thread tid at index tid, so that a wave reads and writes
+// it in whole lines; "tile image": the bytes of the adjoint's LDS tile.
+//   FT   [RF/16][NT] quads      F[16 rt + 4 g + e][16 w + c]
+//   Tau  [L][RF]                tanh(q F^T), plain rows
+//   K    per block [3][16 NB] rows, tile images: beta Kt, Qt, Ki
+//   U    per block [16 NB] rows, tile image: u
+//   C    per block tiles_all(NB) coupling tiles, tile images: P, -A, T
+//   S    [L/16][D/16][NT] quads S'[16 vt + 4 g + e][16 w + c], the block start
+//                               state times the block's reference e^{rho}: entry
+//                               NB m of block m, or (per-tile evaluation) entry
+//                               NB m + i of its tile i
+//   Gam  [L/16][D] f32          e^{rho}, indexed like S
+//   Beta [2][L] f32             beta, then the scalar write gate sigmoid(wx)
+//   E    [L/16][NT] f32x4       e^{lam_t - rho}: t = 16 tt + c, keys 16 w + 4 g + e
+//   Sig  [L/16][NT] quads       the erase gate, same elements
+//   W    [L/16][NT] f32x4       the write gate: t = 16 tt + 4 g + e, value 16 w + c
+//                               (not with the scalar write gate)
+//   V    [L/16][NT] quads       v (activated), same elements
+//   Q    [L/16][NT] quads       q (activated): t = 16 tt + 4 g + e, key 16 w + c
+//   dF   [D][RF] f32            written by the adjoint: the chunk's gradient of F,
+//                               stored transposed (dF[r][j] at (j, r))
+struct ChunkRec {
+  unsigned FT, Tau, K, U, C, S, Gam, Beta, E, Sig, W, V, Q, dF;
+  unsigned total;
+};
+__host__ __device__ constexpr unsigned rec_align(unsigned x) { return (x + 255) & ~255u; }
+// bytes of one [rows][D] tile image and of one block's coupling tiles
+template <typename T, int D>
+__host__ __device__ constexpr unsigned image_bytes(int rows) { return (unsigned)(rows * RowTile<T, D>::LD * (int)sizeof(T)); }
+template <typename T>
+__host__ __device__ constexpr unsigned ctile_bytes(int NB) { return (unsigned)(tiles_all(NB) * SmallTile<T>::N * (int)sizeof(T)); }
+
+template <typename T, int D>
+__host__ __device__ constexpr ChunkRec chunk_rec(int L, int RF, int NB) {
   ChunkRec r{};
-  const size_t nbc = L / 16;
-  size_t off = 0;
-  r.F = off;   off += rec_align((size_t)RF * D * e);
-  r.Tau = off; off += rec_align((size_t)L * RF * e);
-  r.Tm = off;  off += rec_align(nbc * 256 * e);
-  r.P = off;   off += rec_align(nbc * 256 * e);
-  r.S = off;   off += rec_align(nbc * (size_t)D * D * e);
-  r.E = off;   off += rec_align(nbc * 16 * (size_t)D * 4);
-  r.Sig = off; off += rec_align(nbc * 16 * (size_t)D * e);
-  r.dF = off;  off += rec_align((size_t)RF * D * 4);
+  const unsigned e = sizeof(T), nt = L / 16, NT = (D / 16) * 64;
+  unsigned off = 0;
+  r.FT = off;  off += rec_align((RF / 16) * NT * 4 * e);
+  r.Tau = off; off += rec_align(L * RF * e);
+  r.K = off;   off += rec_align(3 * image_bytes<T, D>(L));
+  r.U = off;   off += rec_align(image_bytes<T, D>(L));
+  r.C = off;   off += rec_align((nt / NB) * ctile_bytes<T>(NB));
+  r.S = off;   off += rec_align(nt * D * D * e);
+  r.Gam = off; off += rec_align(nt * D * 4);
+  r.Beta = off; off += rec_align(2 * L * 4);
+  r.E = off;   off += rec_align(nt * NT * 16);
+  r.Sig = off; off += rec_align(nt * NT * 4 * e);
+  r.W = off;   off += rec_align(nt * NT * 16);
+  r.V = off;   off += rec_align(nt * NT * 4 * e);
+  r.Q = off;   off += rec_align(nt * NT * 4 * e);
+  r.dF = off;  off += rec_align(RF * D * 4);
   r.total = off;
   return r;
 }
@@ -88,50 +148,34 @@ constexpr size_t kMaxLdsBytes = 160 * 1024;
 __host__ __device__ constexpr size_t lds_round(size_t x) { return (x + 15) & ~(size_t)15; }
 __host__ __device__ constexpr size_t lds_max(size_t a, size_t b) { return a > b ? a : b; }
 
-// Token contractions (K = LW) run over LK = max(LW, K per MFMA) columns; the
-// padding columns are kept at zero.
-template <typename T, int LW>
-__host__ __device__ constexpr int lk_of() {
-  return (sizeof(T) == 2 && LW < 32) ? 32 : LW;
-}
-
-// LDS layout of the chunk recompute for one sub-chunk of LW tokens (NB = LW / 16
-// blocks); SW: the scalar write gate (RP fold rows instead of 2RP).  Every row is padded by 16 bytes.  Region X holds
-// the copy of the chunk start state while the fold runs and the per-token
-// key-side operands after.  Beta holds beta, then the scalar write gates.
-// Kn (kVarAct) holds per-wave partial sums of the squared activated keys.
+// LDS layout of the chunk recompute for WY blocks of NB 16-token tiles (W = 16 NB
+// tokens).  X holds the chunk start state while the fold reads it, then the
+// block's rows of v and wx until the gates have taken them, then S diag(e^{rho})
+// for its transposition; Kt holds the erase logits, Qt the queries and Ki the
+// keys until the gates replace them with the decayed operands in place.  Beta
+// holds beta, then the scalar write gates.
 struct RecLds {
-  size_t U, Q, F, Tau, Beta, X, S, Kt, Qt, Ki, Gam, AT, Tm, Gate, Kn, total;
+  size_t U, X, Kt, Qt, Ki, F, Tau, C, Gam, Flag, Beta, total;
 };
 
-template <typename T, int D, int LW, int RP, int VAR>
+template <typename T, int D, int RP, int VAR, int NB>
 __host__ __device__ constexpr RecLds rec_lds() {
   RecLds l{};
   const size_t e = sizeof(T);
-  constexpr bool SW = (VAR & kVarScalarW) != 0;
-  constexpr size_t RF = fold_rows(RP, VAR);
-  constexpr size_t NB = LW / 16;
-  constexpr size_t PAD = 16 / sizeof(T);
-  constexpr size_t LDD = D + PAD, LDR = RF + PAD, LDB = 16 + PAD;
+  constexpr size_t RF = fold_rows(RP, VAR), W = 16 * NB;
+  constexpr size_t im = lds_round(image_bytes<T, D>(W));
   size_t off = 0;
-  l.U = off;    off += lds_round(RF * LDD * e);
-  l.Q = off;    off += lds_round(LW * LDD * e);
-  l.F = off;    off += lds_round(RF * LDD * e);
-  l.Tau = off;  off += lds_round(LW * LDR * e);
-  l.Beta = off; off += lds_round((SW ? 2 : 1) * LW * 4);
-  l.X = off;
-  size_t x = 0;
-  l.Kt = off + x;  x += lds_round(LW * LDD * e);
-  l.Qt = off + x;  x += lds_round(LW * LDD * e);
-  l.Ki = off + x;  x += lds_round(LW * LDD * e);
-  l.Gam = off + x; x += lds_round(NB * D * 4);
-  l.AT = off + x;  x += lds_round(NB * 16 * 20 * 4);
-  l.Tm = off + x;  x += lds_round(NB * 16 * LDB * e);
-  l.S = off;
-  x = lds_max(x, lds_round(D * LDD * e));
-  off += x;
-  l.Gate = off; off += lds_round(2 * D * 4);   // -exp(A), tau_f of the head (gated)
-  l.Kn = off;   off += (VAR & kVarAct) ? lds_round((D / 16) * LW * 4) : 0;
+  l.U = off;    off += lds_round(RF * RowTile<T, D>::LD * e);
+  l.X = off;    off += lds_max(lds_round(image_bytes<T, D>(D)), 2 * im);
+  l.Kt = off;   off += im;
+  l.Qt = off;   off += im;
+  l.Ki = off;   off += im;
+  l.F = off;    off += lds_round(RF * RowTile<T, D>::LD * e);
+  l.Tau = off;  off += lds_round(W * RowTile<T, (int)RF>::LD * e);
+  l.C = off;    off += lds_round(ctile_bytes<T>(NB));
+  l.Gam = off;  off += lds_round((size_t)NB * D * 4);
+  l.Flag = off; off += lds_round(16 * 4);
+  l.Beta = off; off += lds_round(2 * W * 4);
   l.total = off;
   return l;
 }
@@ -246,7 +290,8 @@ struct BwdArgs {
   float* part;    // per-(b,h, chunk split) partial d[Ub; Uw] (workspace)
   float* partV;   // per-(b,h,split) partial dVb, dVw (workspace)
   const void* rec;  // chunk records of the recompute (workspace)
-  int B, T, H, R, RP, L;
+  void* opnd;       // per-(b,h) operand quads of the parameters (workspace, adj_opnd_bytes each)
+  int B, T, H, R, RP, L, NB;   // NB: 16-token tiles of a WY block of the backward
   int wait_limit;   // polls of the adjoint's bounded wait for a chunk record
 };
 
@@ -255,101 +300,63 @@ struct BwdArgs {
 constexpr int kVSplit = 16;
 constexpr int kUSplit = 16;
 
-// LDS layout of the adjoint kernel (one 16-token block at a time); SW: the
-// scalar write gate (RP fold rows instead of 2RP, no Vw).  The four [value][token]
-// exchange buffers dOT .. dzwT are dead between the end of one block and the
-// value-side step of the next; the block's token tiles (k, q, bx, v, dO and,
-// unless the write gate is scalar, wx, in the token dtype, then g in f32: 16
-// rows each, unpadded, 16-byte chunks XOR-swizzled by row) are staged there
-// (Stage), so the region holds at least 6 (5) * 16 * D elements plus 16 * D
-// floats.  Except in gated kernels, the bx and g slots hold the block's erase
-// gate and retention factors E from the chunk record instead.  At a chunk start the glue reuses dSx for dF as a high and a low
-// part ([D][LDF] each).
-// Gated kernels stage the decay logit f (token dtype) in place of g and keep
-// -exp(A), tau_f of the head (Gate) behind it, inside the area g would take
-// where that is large enough.  Beta holds beta, then the scalar write gates;
-// Dwx the per-wave partial sums of the scalar write gate's gradient.
-// Inv (kVarAct) holds the inverse L2 norms of the block's activated keys and
-// queries.
-struct BwdLds {
-  size_t F, VbT, VwT, Tau, Tm, P, Gam, Beta, Dbeta, Dwx, Inv, Kt, Qt, Ki, Sx, dSx, dOT, uT, dRT, dzwT, Stage,
-      Gate, dzb, dY, total;
+// LDS layout of the adjoint for WY blocks of NB 16-token tiles (W = 16 NB
+// tokens).  dM holds the state gradient for the key side, then (from the
+// pair-term step on) the write-logit gradients dz_w and, behind them, dY; R the
+// exchanged -dR, then dz_b; C the block's coupling tiles, then dA and dP; U and
+// dO at a chunk start the two token-dtype parts of dF.  Dbeta and Dwx hold one
+// row of partial sums per wave.
+struct AdjLds {
+  size_t Kt, Qt, Ki, U, dO, dM, R, C, dY, Dbeta, Dwx, Beta, Ws, Gam, Ctl, total;
 };
 
-// token tiles the adjoint stages per block
-__host__ __device__ constexpr int bwd_stage_tiles(bool SW) { return SW ? 5 : 6; }
-
-// Whether the adjoint lays its bf16 operand tiles out bank-conflict-free (the
-// quad swizzle qswz).  Not in the gated kernel with the per-channel write
-// gate: its extra live state leaves no registers for the swizzle's address
-// terms (they raise its spills and cost more than the conflicts they remove).
-template <typename T, int VAR>
-__host__ __device__ constexpr bool bwd_qswz() {
-  return sizeof(T) == 2 && (VAR & (kVarGated | kVarScalarW)) != kVarGated;
-}
-// Row strides (elements): Kt, Qt, Ki, VbT, VwT (the quad swizzle needs a stride
-// of 4 (mod 8) quads; otherwise a 16-byte pad) ...
-template <typename T, int D, int VAR>
-__host__ __device__ constexpr int bwd_ldk() { return bwd_qswz<T, VAR>() ? D + 16 : D + 16 / (int)sizeof(T); }
-// ... the [value][token] exchange tiles ...
-template <typename T, int VAR>
-__host__ __device__ constexpr int bwd_ldx() { return bwd_qswz<T, VAR>() ? 16 : 16 + 16 / (int)sizeof(T); }
-// ... and S, dS' of the block: unpadded rows with the hswz128 swizzle at
-// bf16 d = 128, padded rows otherwise
-template <typename T, int D, int VAR>
-__host__ __device__ constexpr bool bwd_sx_hswz() { return bwd_qswz<T, VAR>() && D == 128; }
-template <typename T, int D, int VAR>
-__host__ __device__ constexpr int bwd_ldsx() { return bwd_sx_hswz<T, D, VAR>() ? D : D + 16 / (int)sizeof(T); }
-
-template <typename T, int D, int RP, int VAR>
-__host__ __device__ constexpr BwdLds bwd_lds() {
-  BwdLds l{};
+template <typename T, int D, int RP, int VAR, int NB>
+__host__ __device__ constexpr AdjLds adj_lds() {
+  AdjLds l{};
   const size_t e = sizeof(T);
   constexpr bool SW = (VAR & kVarScalarW) != 0;
-  constexpr size_t RF = fold_rows(RP, VAR);
-  constexpr size_t NW = D / 16;
-  constexpr size_t PAD = 16 / sizeof(T);
-  constexpr size_t LDD = D + PAD, LDR = RF + PAD, LDB = 16 + PAD;
-  constexpr size_t NS = bwd_stage_tiles(SW);
+  constexpr size_t RF = fold_rows(RP, VAR), W = 16 * NB, NW = D / 16;
+  constexpr size_t im = lds_round(image_bytes<T, D>(W));
   size_t off = 0;
-  constexpr size_t LDK = bwd_ldk<T, D, VAR>(), LDX = bwd_ldx<T, VAR>(), LDSX = bwd_ldsx<T, D, VAR>();
-  l.F = off;     off += lds_round(RF * LDD * e);
-  l.VbT = off;   off += lds_round(RP * LDK * e);
-  l.VwT = off;   off += lds_round((RF - RP) * LDK * e);
-  l.Tau = off;   off += lds_round(16 * LDR * e);
-  l.Tm = off;    off += lds_round(16 * LDB * e);
-  l.P = off;     off += lds_round(16 * LDB * e);
+  l.Kt = off;    off += im;
+  l.Qt = off;    off += im;
+  l.Ki = off;    off += im;
+  l.U = off;     off += im;
+  l.dO = off;    off += im;
+  // dF parts over U and dO: bf16 two unpadded [D][RF] tiles, f32 one padded
+  constexpr size_t df = sizeof(T) == 2 ? 2 * D * RF * 2 : (size_t)D * (RF + 4) * 4;
+  off = lds_max(off, l.U + lds_round(df));
+  l.dM = off;
+  l.dY = l.dM + (SW ? 0 : im);
+  off += lds_max(lds_round(image_bytes<T, D>(D)), (SW ? 0 : im) + lds_round(W * RowTile<T, (int)RF>::LD * e));
+  l.R = off;     off += im;
+  l.C = off;     off += lds_round(lds_max(ctile_bytes<T>(NB), (size_t)2 * tiles_p(NB) * SmallTile<T>::N * e));
+  l.Dbeta = off; off += lds_round(NW * W * 4);
+  l.Dwx = off;   off += SW ? lds_round(NW * W * 4) : 0;
+  l.Beta = off;  off += lds_round(W * 4);
+  l.Ws = off;    off += SW ? lds_round(W * 4) : 0;
   l.Gam = off;   off += lds_round(D * 4);
-  l.Beta = off;  off += lds_round((SW ? 32 : 16) * 4);
-  l.Dbeta = off; off += lds_round((NW + 1) * 16 * 4);   // NW value partials + the A part
-  l.Dwx = off;   off += SW ? lds_round(NW * 16 * 4) : 0;
-  l.Inv = off;   off += (VAR & kVarAct) ? lds_round(2 * 16 * 4) : 0;
-  l.Kt = off;    off += lds_round(16 * LDK * e);
-  l.Qt = off;    off += lds_round(16 * LDK * e);
-  l.Ki = off;    off += lds_round(16 * LDK * e);
-  l.Sx = off;    off += lds_round(D * LDSX * e);
-  constexpr size_t LDF = RF + 4;
-  l.dSx = off;   off += lds_round(D * lds_max(LDSX, 2 * LDF) * e);
-  l.Stage = off;
-  l.dOT = off;   off += lds_round(D * LDX * e);
-  l.uT = off;    off += lds_round(D * LDX * e);
-  l.dRT = off;   off += lds_round(D * LDX * e);
-  l.dzwT = off;  off += lds_round(D * LDX * e);
-  {
-    const size_t garea = l.Stage + lds_round(NS * 16 * D * e);     // g, or f then Gate
-    l.Gate = garea + lds_round(16 * D * e);
-    off = lds_max(off, garea + lds_max(lds_round(16 * D * 4), lds_round(16 * D * e) + lds_round(2 * D * 4)));
-  }
-  l.dzb = off;   off += lds_round(16 * LDD * e);
-  l.dY = off;    off += lds_round(16 * LDR * e);
+  l.Ctl = off;   off += 16;
   l.total = off;
   return l;
 }
 
 // LDS of the fused chunk recompute + adjoint launch
-template <typename T, int D, int LW, int RP, int VAR>
+template <typename T, int D, int RP, int VAR, int NB>
 __host__ __device__ constexpr size_t fused_lds() {
-  return lds_max(rec_lds<T, D, LW, RP, VAR>().total, bwd_lds<T, D, RP, VAR>().total);
+  return lds_max(rec_lds<T, D, RP, VAR, NB>().total, adj_lds<T, D, RP, VAR, NB>().total);
+}
+
+// bytes of one adjoint workgroup's parameter operands: V^T of the dtau tiles (RF
+// x D spread over the waves, at least one fold row tile each) and [Ub; Uw] (RF
+// x D) as token-dtype quads, then -exp(A) and tau_f (gated) as f32 vectors, all
+// in thread order
+__host__ __device__ constexpr size_t adj_opnd_quads(int D, int RF) {
+  const size_t nw = D / 16, nrt = RF / 16, nvs = nrt < nw ? 1 : nrt / nw;
+  return (nvs * nw + nrt) * nw * 64;
+}
+__host__ __device__ constexpr size_t adj_opnd_bytes(int D, int RF, size_t e) {
+  return adj_opnd_quads(D, RF) * 4 * e + 2 * (size_t)(D / 16) * 64 * 16;
 }
 
 // Chunk recompute and adjoint in one launch (see carve_bwd.h).  f carries the
@@ -357,17 +364,18 @@ __host__ __device__ constexpr size_t fused_lds() {
 // at sync_ints(B * H, T / L) ints of workspace, zeroed by launch_sync_clear
 // on the same stream before; cus is the device's compute-unit count.
 // launch_bwd_fused dispatches on var to launch_bwd_fused_var<VAR>.
-int launch_bwd_fused(const FwdArgs& f, const BwdArgs& a, int* sync, int cus, int dtype, int D, int LW,
+int launch_bwd_fused(const FwdArgs& f, const BwdArgs& a, int* sync, int cus, int dtype, int D, int NB,
                      int var, hipStream_t s);
 template <int VAR>
-int launch_bwd_fused_var(const FwdArgs& f, const BwdArgs& a, int* sync, int cus, int dtype, int D, int LW,
+int launch_bwd_fused_var(const FwdArgs& f, const BwdArgs& a, int* sync, int cus, int dtype, int D, int NB,
                          hipStream_t s);
 // dA[h][j], dtau[h][j] = sums over b (in order) of the per-(b,h) partials
 int launch_gate_reduce(const float* partG, int B, int H, int D, float* dA, float* dtau, hipStream_t s);
 int launch_sync_clear(int* sync, size_t n, hipStream_t s);
-// LDS bytes of the fused launch of the default variant with LW-token
-// recompute sub-chunks (2RP fold rows)
-size_t bwd_lds_bytes(int dtype, int D, int LW, int RP);
+// LDS bytes of the fused launch with WY blocks of NB 16-token tiles (the
+// largest over the variants), and bytes of one chunk record
+size_t bwd_lds_bytes(int dtype, int D, int NB, int RP);
+size_t chunk_rec_bytes(int dtype, int D, int L, int RF, int NB);
 // ints of the synchronisation area: one ready flag per chunk, the ticket
 // counter that assigns the workgroup roles, the wait-timeout word (nonzero once
 // an adjoint wave's bounded wait for a record ran out), padding, then per

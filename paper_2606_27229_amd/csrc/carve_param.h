@@ -40,7 +40,7 @@ __device__ __forceinline__ void uparam_item(const BwdArgs& a, const int item, ch
   const int Tn = a.T, L = a.L, R = a.R;
   const int bh = item / kUSplit, split = item % kUSplit;
   const int nch = Tn / L;
-  const ChunkRec cr = chunk_rec(sizeof(T), D, L, R2);
+  const ChunkRec cr = chunk_rec<T, D>(L, R2, a.NB);
   const char* recb = reinterpret_cast<const char*>(a.rec) + (size_t)bh * nch * cr.total;
   f32x4 acc[NRT];
   for (int rt = 0; rt < NRT; ++rt) acc[rt] = zero4();
@@ -123,7 +123,7 @@ __device__ __forceinline__ void vparam_item(const BwdArgs& a, const int item, ch
   const int rs = H * D;
   const T* __restrict__ dbx = reinterpret_cast<const T*>(a.dbx) + bh0;
   const T* __restrict__ dwx = reinterpret_cast<const T*>(a.dwx) + bh0;
-  const ChunkRec cr = chunk_rec(sizeof(T), D, L, R2);
+  const ChunkRec cr = chunk_rec<T, D>(L, R2, a.NB);
   const char* recb = reinterpret_cast<const char*>(a.rec) + (size_t)bh * nch * cr.total;
 
   f32x4 accB[NRB], accW[NRB];
