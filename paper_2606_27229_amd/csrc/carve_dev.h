@@ -222,6 +222,17 @@ __device__ __forceinline__ f32x4 gload4(const bf16_t* p) {
 }
 __device__ __forceinline__ f32x4 gload4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 
+// Row and column of tile y of a row-major enumeration of the lower-triangular
+// 16-token tiles of a block of up to four: inclusive (j <= i) or strict (j < i).
+// From packed digits: the tile loops are short and wave-uniform, and counting
+// rows with compares and branches took as long as the tile's products.
+__device__ __forceinline__ int tri_row_of(int y, bool strict) {
+  return (int)((strict ? 0x333221ull : 0x3333222110ull) >> (4 * y)) & 15;
+}
+__device__ __forceinline__ int tri_col_of(int y, bool strict) {
+  return (int)((strict ? 0x210100ull : 0x3210210100ull) >> (4 * y)) & 15;
+}
+
 // Chunk-record accesses between compute units of different XCDs: buffer
 // operations at agent scope (sc1).  Such a store goes through the XCD's L2 to
 // the coherence point, and such a load comes from there, so that publishing a

@@ -66,27 +66,6 @@
 
 namespace carve {
 
-// Tile x of a row-major enumeration of the lower-triangular tiles (i, j):
-// strict (j < i, starting at i = 1) or inclusive (j <= i).
-__host__ __device__ constexpr int tri_row(int x, bool strict) {
-  int i = strict ? 1 : 0;
-  while (x >= (strict ? i : i + 1)) {
-    x -= strict ? i : i + 1;
-    ++i;
-  }
-  return i;
-}
-__host__ __device__ constexpr int tri_col(int x, bool strict) {
-  int i = strict ? 1 : 0;
-  while (x >= (strict ? i : i + 1)) {
-    x -= strict ? i : i + 1;
-    ++i;
-  }
-  return x;
-}
-static_assert(tri_row(0, true) == 1 && tri_col(0, true) == 0 && tri_row(5, true) == 3 && tri_col(5, true) == 2, "");
-static_assert(tri_row(0, false) == 0 && tri_row(2, false) == 1 && tri_col(2, false) == 1 && tri_col(9, false) == 3, "");
-
 // q * f (per-element factors at p), rounded back to the operand type
 template <typename T>
 __device__ __forceinline__ typename Quad<T>::q scale_q(typename Quad<T>::q q, const float* p) {
@@ -347,7 +326,8 @@ __global__ void __launch_bounds__(fwd_threads(D)) carve_chain_fwd_kernel(FwdArgs
         asm volatile("" : "+v"(cs_), "+v"(gs_));                                   \
         const bool odd_ = (cs_ & 1) != 0;                                          \
         float* r0_ = a.S_chunks + ((size_t)bh * (Tn / L) + blk / bpc) * D * D + (16 * w + (cs_ & ~1)) * D + 4 * gs_ + (odd_ ? 16 : 0); \
-        for (int m_ = (JT0_) / 2; m_ < (JT1_) / 2; ++m_) {                         \
+        _Pragma("unroll") for (int m_ = 0; m_ < NJT / 2; ++m_) {                   \
+          if (m_ < (JT0_) / 2 || m_ >= (JT1_) / 2) continue;                       \
           f32x4 st0_, st1_;                                                        \
           for (int e_ = 0; e_ < 4; ++e_) {                                         \
             const float rv_ = lane_xor1(odd_ ? St[2 * m_][e_] : St[2 * m_ + 1][e_]); \
@@ -669,44 +649,76 @@ __global__ void __launch_bounds__(fwd_threads(D)) carve_chain_fwd_kernel(FwdArgs
       }
     }
     if (NOW == NW || w < NOW) {
-      // off-diagonal tiles of -A and all tiles of P, stored [t][s]; a scalar
-      // loop over this wave's tiles (addresses from opaque lane coordinates)
+      // off-diagonal tiles of -A and all tiles of P, stored [t][s], two at a
+      // time: the products of one tile are a chain of four behind their LDS
+      // reads, and this loop is the step's longest path (one tile at a time it
+      // took 5500 of the block's 25700 cycles at d = 128, 64 tokens).  Addresses
+      // come from opaque lane coordinates.
       int ct = c, gt = g;
       asm volatile("" : "+v"(ct), "+v"(gt));
-#pragma unroll 1
-      for (int x = w; x < NTA + NTP; x += NOW) {
-        const bool isA = x < NTA;
-        const int y = isA ? x : x - NTA;
-        const int i = tri_row(y, isA), j = tri_col(y, isA);
-        // acc[e] = Ki_{s = 16 j + 4 g + e} . X_{t = 16 i + c}, X = Kt (A) or Qt (P)
-        const T* ar = sKi + (16 * j + ct) * LDD + ((4 * gt) ^ CARVE_QX(ct));
-        const T* br = (isA ? sKt : sQ) + (16 * i + ct) * LDD + ((4 * gt) ^ CARVE_QX(ct));
-        f32x4 acc = zero4();
-        if (wide && i > j) {
-          // per-tile references: Ki e^{c_j - m_j} against X e^{m_i - c_j}; lane
-          // quads hold channels 32 jp + 4 g .. + 3 and 16 further
-          const float* fa = sTab + (kTabHalf + j) * D + 4 * gt;
-          const float* fb = sTab + (i == j + 1 ? kTabHalf + i : kTabGap + (i - 2) * (i - 1) / 2 + j) * D + 4 * gt;
-          for (int jp = 0; jp < D / 32; ++jp) {
-            const quad a0 = scale_q<T>(Qd::ld(ar + 32 * jp), fa + 32 * jp);
-            const quad a1 = scale_q<T>(Qd::ld(ar + 32 * jp + 16), fa + 32 * jp + 16);
-            const quad b0 = scale_q<T>(Qd::ld(br + 32 * jp), fb + 32 * jp);
-            const quad b1 = scale_q<T>(Qd::ld(br + 32 * jp + 16), fb + 32 * jp + 16);
-            acc = Qd::mma32(a0, a1, b0, b1, acc);
-          }
-        } else {
-          for (int jp = 0; jp < D / 32; ++jp)
-            acc = Qd::mma32(Qd::ld(ar + 32 * jp), Qd::ld(ar + 32 * jp + 16), Qd::ld(br + 32 * jp),
-                            Qd::ld(br + 32 * jp + 16), acc);
-        }
+      const auto put_tile = [&](int x, int i, int j, f32x4 acc) {
         f32x4 val;
-        if (isA) {
+        if (x < NTA) {
           const float bt = bcur[16 * i + ct];
           for (int e = 0; e < 4; ++e) val[e] = -bt * acc[e];
           Qd::st(sA + (16 * i + ct) * LDW + 16 * j + ((4 * gt) ^ CARVE_QX(ct)), Qd::cvt(val));
         } else {
           for (int e = 0; e < 4; ++e) val[e] = (i > j || 4 * gt + e <= ct) ? acc[e] : 0.0f;
           Qd::st(sP + (16 * i + ct) * LDW + 16 * j + ((4 * gt) ^ CARVE_QX(ct)), Qd::cvt(val));
+        }
+      };
+      constexpr int NTT = NTA + NTP;
+      if (!wide) {
+#pragma unroll 1
+        for (int x0 = w; x0 < NTT; x0 += 2 * NOW) {
+          // (past the end the second tile repeats the first)
+          const int x1 = x0 + NOW < NTT ? x0 + NOW : x0;
+          const bool a0 = x0 < NTA, a1 = x1 < NTA;
+          const int i0 = tri_row_of(a0 ? x0 : x0 - NTA, a0), j0 = tri_col_of(a0 ? x0 : x0 - NTA, a0);
+          const int i1 = tri_row_of(a1 ? x1 : x1 - NTA, a1), j1 = tri_col_of(a1 ? x1 : x1 - NTA, a1);
+          // acc[e] = Ki_{s = 16 j + 4 g + e} . X_{t = 16 i + c}, X = Kt (A) or Qt (P)
+          const T* ar0 = sKi + (16 * j0 + ct) * LDD + ((4 * gt) ^ CARVE_QX(ct));
+          const T* br0 = (a0 ? sKt : sQ) + (16 * i0 + ct) * LDD + ((4 * gt) ^ CARVE_QX(ct));
+          const T* ar1 = sKi + (16 * j1 + ct) * LDD + ((4 * gt) ^ CARVE_QX(ct));
+          const T* br1 = (a1 ? sKt : sQ) + (16 * i1 + ct) * LDD + ((4 * gt) ^ CARVE_QX(ct));
+          f32x4 acc0 = zero4(), acc1 = zero4();
+          for (int jp = 0; jp < D / 32; ++jp) {
+            acc0 = Qd::mma32(Qd::ld(ar0 + 32 * jp), Qd::ld(ar0 + 32 * jp + 16), Qd::ld(br0 + 32 * jp),
+                             Qd::ld(br0 + 32 * jp + 16), acc0);
+            acc1 = Qd::mma32(Qd::ld(ar1 + 32 * jp), Qd::ld(ar1 + 32 * jp + 16), Qd::ld(br1 + 32 * jp),
+                             Qd::ld(br1 + 32 * jp + 16), acc1);
+          }
+          put_tile(x0, i0, j0, acc0);
+          put_tile(x1, i1, j1, acc1);
+        }
+      } else {
+        // some channel on per-tile references
+#pragma unroll 1
+        for (int x = w; x < NTT; x += NOW) {
+          const bool isA = x < NTA;
+          const int y = isA ? x : x - NTA;
+          const int i = tri_row_of(y, isA), j = tri_col_of(y, isA);
+          const T* ar = sKi + (16 * j + ct) * LDD + ((4 * gt) ^ CARVE_QX(ct));
+          const T* br = (isA ? sKt : sQ) + (16 * i + ct) * LDD + ((4 * gt) ^ CARVE_QX(ct));
+          f32x4 acc = zero4();
+          if (i > j) {
+            // Ki e^{c_j - m_j} against X e^{m_i - c_j}; lane quads hold channels
+            // 32 jp + 4 g .. + 3 and 16 further
+            const float* fa = sTab + (kTabHalf + j) * D + 4 * gt;
+            const float* fb = sTab + (i == j + 1 ? kTabHalf + i : kTabGap + (i - 2) * (i - 1) / 2 + j) * D + 4 * gt;
+            for (int jp = 0; jp < D / 32; ++jp) {
+              const quad a0 = scale_q<T>(Qd::ld(ar + 32 * jp), fa + 32 * jp);
+              const quad a1 = scale_q<T>(Qd::ld(ar + 32 * jp + 16), fa + 32 * jp + 16);
+              const quad b0 = scale_q<T>(Qd::ld(br + 32 * jp), fb + 32 * jp);
+              const quad b1 = scale_q<T>(Qd::ld(br + 32 * jp + 16), fb + 32 * jp + 16);
+              acc = Qd::mma32(a0, a1, b0, b1, acc);
+            }
+          } else {
+            for (int jp = 0; jp < D / 32; ++jp)
+              acc = Qd::mma32(Qd::ld(ar + 32 * jp), Qd::ld(ar + 32 * jp + 16), Qd::ld(br + 32 * jp),
+                              Qd::ld(br + 32 * jp + 16), acc);
+          }
+          put_tile(x, i, j, acc);
         }
       }
     }
