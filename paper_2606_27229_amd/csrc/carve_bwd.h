@@ -388,22 +388,26 @@ struct Adjoint {
       E[tt] = rc.template ld<f32x4>(cr.E + (tile0 + tt) * NT * 16, tid * 16);
       sig[tt] = rc.template ld<quad>(cr.Sig + (tile0 + tt) * NT * QB, tid * QB);
     }
-    // dA = -dR u^T (s < t) and dP = dO u^T (s <= t), stored as rows of t
+    // dA = -dR u^T (s < t) and dP = dO u^T (s <= t), stored as rows of t: a wave
+    // takes both tiles of a pair (i, j), which share u's rows
 #pragma unroll 1
-    for (int x = w; x < 2 * NTP; x += NW) {
-      const bool isP = x >= NTP;
-      int i = 0, j = isP ? x - NTP : x;
-      while (j >= i + 1) {
-        j -= i + 1;
-        ++i;
+    for (int x = w; x < NTP; x += NW) {
+      const int i = tri_row_of(x, false), j = tri_col_of(x, false);
+      const T* pu = sU + RT::at(16 * j + c, 0, 4 * g);
+      const T* pr = sR + RT::at(16 * i + c, 0, 4 * g);
+      const T* po = sdO + RT::at(16 * i + c, 0, 4 * g);
+      f32x4 accA = zero4(), accP = zero4();
+      for (int vp = 0; vp < NJT / 2; ++vp) {
+        const quad u0 = Qd::ld(pu + 32 * vp), u1 = Qd::ld(pu + 32 * vp + 16);
+        accA = Qd::mma32(u0, u1, Qd::ld(pr + 32 * vp), Qd::ld(pr + 32 * vp + 16), accA);
+        accP = Qd::mma32(u0, u1, Qd::ld(po + 32 * vp), Qd::ld(po + 32 * vp + 16), accP);
       }
-      const T* b = isP ? sdO : sR;
-      f32x4 acc = zero4();
-      for (int vp = 0; vp < NJT / 2; ++vp)
-        acc = Qd::mma32(Qd::ld(sU + RT::at(16 * j + c, 32 * vp, 4 * g)), Qd::ld(sU + RT::at(16 * j + c, 32 * vp + 16, 4 * g)),
-                        Qd::ld(b + RT::at(16 * i + c, 32 * vp, 4 * g)), Qd::ld(b + RT::at(16 * i + c, 32 * vp + 16, 4 * g)), acc);
-      for (int e = 0; e < 4; ++e) acc[e] = (i > j || 4 * g + e < c + (isP ? 1 : 0)) ? acc[e] : 0.0f;
-      Qd::st(sC + x * ST::N + ST::at(c, 4 * g), Qd::cvt(acc));
+      for (int e = 0; e < 4; ++e) {
+        accA[e] = (i > j || 4 * g + e < c) ? accA[e] : 0.0f;
+        accP[e] = (i > j || 4 * g + e <= c) ? accP[e] : 0.0f;
+      }
+      Qd::st(sC + x * ST::N + ST::at(c, 4 * g), Qd::cvt(accA));
+      Qd::st(sC + (NTP + x) * ST::N + ST::at(c, 4 * g), Qd::cvt(accP));
     }
     f32x4 y[NB], dQ[NB], dKi[NB];
     float dgs = 0.0f;   // sum_v dM[v][j] S'[v][j] for j = 16 w + c

@@ -502,11 +502,8 @@ __device__ __forceinline__ void rec_run(const FwdArgs& a, const int first, const
 #pragma unroll 1
         for (int x = w; x < NTP + NTA; x += NOW) {
           const bool isA = x >= NTP;
-          int i = isA ? 1 : 0, j = isA ? x - NTP : x;
-          while (j >= (isA ? i : i + 1)) {
-            j -= isA ? i : i + 1;
-            ++i;
-          }
+          const int y = isA ? x - NTP : x;
+          const int i = tri_row_of(y, isA), j = tri_col_of(y, isA);
           // acc[e] = Ki_{s = 16 j + 4 g + e} . X_{t = 16 i + c}, X = Kh (A) or Qt (P)
           const T* bsrc = isA ? sKt : sQt;
           f32x4 acc = zero4();
