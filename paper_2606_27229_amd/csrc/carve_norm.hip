@@ -89,36 +89,66 @@ __global__ void __launch_bounds__(64 * kNormWaves)
 }
 
 // grid: nwg workgroups; partial[blockIdx.x][N] f32 receives the workgroup's
-// dweight share (its waves summed in order)
+// dweight share (its waves summed in order).  Bound by HBM (two rows read, one
+// written): a wave keeps its columns of the weight in registers for all its
+// rows, and the next row is on its way while the current one's two wave sums
+// run, up to 32 columns per lane (norm_bwd_ahead; 64 would not fit the
+// registers and take each row as it comes).  Forward, backward and sum of the
+// partial rows together at 16384 rows of 2048 bf16: 97 us without the row ahead
+// and with 1024 workgroups, 77 us now.
+template <typename T, int NCH>
+constexpr bool norm_bwd_ahead() { return NCH * NormVec<T>::n <= 32; }
+
 template <typename T, int NCH>
 __global__ void __launch_bounds__(64 * kNormWaves)
     carve_rmsnorm_bwd_kernel(const T* __restrict__ x, const float* __restrict__ wt, const T* __restrict__ dy,
                              T* __restrict__ dx, float* __restrict__ partial, long rows, int N, float eps) {
   typedef typename NormVec<T>::v vec;
   constexpr int VEC = NormVec<T>::n;
+  constexpr bool AHEAD = norm_bwd_ahead<T, NCH>();
   extern __shared__ __attribute__((aligned(16))) char smem[];
   float* sacc = reinterpret_cast<float*>(smem);   // [kNormWaves][N]
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const long stride = (long)gridDim.x * kNormWaves;
-  float acc[NCH][VEC];
+  float acc[NCH][VEC], wr[AHEAD ? NCH : 1][VEC];
 #pragma unroll
-  for (int ch = 0; ch < NCH; ++ch)
+  for (int ch = 0; ch < NCH; ++ch) {
+    const int c0 = (ch * 64 + lane) * VEC;
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) acc[ch][e] = 0.0f;
-  for (long row = (long)blockIdx.x * kNormWaves + wv; row < rows; row += stride) {
-    const T* xr = x + row * N;
-    const T* dyr = dy + row * N;
-    vec xv[NCH], dv[NCH];
-    float ss = 0.0f;
+    for (int e = 0; e < VEC; ++e) {
+      acc[ch][e] = 0.0f;
+      if constexpr (AHEAD) wr[ch][e] = c0 < N ? wt[c0 + e] : 0.0f;
+    }
+  }
+  vec xn[NCH], dn[NCH];   // the next row of this wave
+  const auto load = [&](long row) {
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
       const int c0 = (ch * 64 + lane) * VEC;
       if (c0 < N) {
-        xv[ch] = *reinterpret_cast<const vec*>(xr + c0);
-        dv[ch] = *reinterpret_cast<const vec*>(dyr + c0);
+        xn[ch] = *reinterpret_cast<const vec*>(x + row * N + c0);
+        dn[ch] = *reinterpret_cast<const vec*>(dy + row * N + c0);
+      }
+    }
+  };
+  const long row0 = (long)blockIdx.x * kNormWaves + wv;
+  if (AHEAD && row0 < rows) load(row0);
+  for (long row = row0; row < rows; row += stride) {
+    if (!AHEAD) load(row);
+    vec xv[NCH], dv[NCH];
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+      xv[ch] = xn[ch];
+      dv[ch] = dn[ch];
+    }
+    if (AHEAD && row + stride < rows) load(row + stride);
+    float ss = 0.0f;
+#pragma unroll
+    for (int ch = 0; ch < NCH; ++ch) {
+      const int c0 = (ch * 64 + lane) * VEC;
+      if (c0 < N)
 #pragma unroll
         for (int e = 0; e < VEC; ++e) ss += (float)xv[ch][e] * (float)xv[ch][e];
-      }
     }
     const float r = 1.0f / sqrtf(wave_sum(ss) / (float)N + eps);
     float dot = 0.0f;
@@ -129,7 +159,7 @@ __global__ void __launch_bounds__(64 * kNormWaves)
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
           const float n = (float)xv[ch][e] * r, d = (float)dv[ch][e];
-          dot += d * wt[c0 + e] * n;
+          dot += d * (AHEAD ? wr[AHEAD ? ch : 0][e] : wt[c0 + e]) * n;
           acc[ch][e] += d * n;
         }
       }
@@ -144,7 +174,7 @@ __global__ void __launch_bounds__(64 * kNormWaves)
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
           const float n = (float)xv[ch][e] * r;
-          o[e] = (T)(r * ((float)dv[ch][e] * wt[c0 + e] - n * m));
+          o[e] = (T)(r * ((float)dv[ch][e] * (AHEAD ? wr[AHEAD ? ch : 0][e] : wt[c0 + e]) - n * m));
         }
         *reinterpret_cast<vec*>(dxr + c0) = o;
       }
@@ -215,8 +245,11 @@ int launch_fwd_t(const void* x, const float* wt, void* y, long rows, int N, floa
 }
 
 template <typename T, int NCH>
-int launch_bwd_t(const void* x, const float* wt, const void* dy, void* dx, float* partial, int nwg, long rows, int N,
+int launch_bwd_t(const void* x, const float* wt, const void* dy, void* dx, float* partial, int& nwg, long rows, int N,
                  float eps, hipStream_t s) {
+  // with 32 columns per lane two workgroups fit a compute unit at a time: half
+  // the workgroups, each with twice the rows, and half the partial rows to sum
+  if (norm_bwd_ahead<T, NCH>() && NCH * NormVec<T>::n == 32 && nwg > kNormBwdGroups / 2) nwg = kNormBwdGroups / 2;
   const size_t lds = (size_t)kNormWaves * N * sizeof(float);
   hipLaunchKernelGGL((carve_rmsnorm_bwd_kernel<T, NCH>), dim3((unsigned)nwg), dim3(64 * kNormWaves), lds, s,
                      reinterpret_cast<const T*>(x), wt, reinterpret_cast<const T*>(dy), reinterpret_cast<T*>(dx),
@@ -236,7 +269,7 @@ int launch_fwd_d(const void* x, const float* wt, void* y, long rows, int N, floa
 }
 
 template <typename T>
-int launch_bwd_d(const void* x, const float* wt, const void* dy, void* dx, float* partial, int nwg, long rows, int N,
+int launch_bwd_d(const void* x, const float* wt, const void* dy, void* dx, float* partial, int& nwg, long rows, int N,
                  float eps, hipStream_t s) {
   switch (nch_of<T>(N)) {
     case 1: return launch_bwd_t<T, 1>(x, wt, dy, dx, partial, nwg, rows, N, eps, s);
@@ -267,7 +300,7 @@ int launch_rmsnorm_fwd(const void* x, const float* wt, void* y, long rows, int N
 
 int launch_rmsnorm_bwd(const void* x, const float* wt, const void* dy, void* dx, float* partial, float* dw, long rows,
                        int N, float eps, int dtype, hipStream_t s, void (*mark)(hipStream_t)) {
-  const int nwg = rmsnorm_bwd_groups(rows);
+  int nwg = rmsnorm_bwd_groups(rows);   // (the launch may take fewer)
   const int st = dtype == CARVE_BF16 ? launch_bwd_d<bf16_t>(x, wt, dy, dx, partial, nwg, rows, N, eps, s)
                                      : launch_bwd_d<float>(x, wt, dy, dx, partial, nwg, rows, N, eps, s);
   if (st) return st;

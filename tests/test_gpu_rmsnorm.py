@@ -57,6 +57,22 @@ def test_rmsnorm_parity(dtype, B, T, H, Dv):
     assert max(errs.values()) <= TOL[dtype], errs
 
 
+@pytest.mark.parametrize("dtype,N", [("bf16", 2048), ("bf16", 1544), ("f32", 2048), ("f32", 1028)])
+@pytest.mark.parametrize("rows", [1, 5, 2047, 2049, 4097, 6150])
+def test_rmsnorm_rows_per_wave(dtype, N, rows):
+    """Row lengths of 32 columns per lane (whole, and with idle lanes) over the
+    512 workgroups of four waves: fewer rows than waves, one more than a wave
+    each, and ragged counts of two and four.  dweight is an f32 sum of the rows'
+    f32 products for both dtypes: 1e-5 of its largest value."""
+    print(f"case rmsnorm rows {dtype} N={N} rows={rows}", flush=True)
+    o, dy, w = _inputs(1, rows, 1, N, dtype, seed=rows + N)
+    _, d_o, dw = _run(o, dy, w, dtype)
+    rdo, rdw = orc.rmsnorm_bwd(o, w, dy)
+    errs = {"d_o": max_rel(d_o, rdo), "dweight": max_rel(dw, rdw)}
+    print("max-rel errors:", {k: float("%.3g" % e) for k, e in errs.items()}, flush=True)
+    assert errs["d_o"] <= TOL[dtype] and errs["dweight"] <= 1e-5, errs
+
+
 def test_rmsnorm_headline_layer_output():
     """The norm of the headline layer's own output (B=4 H=16 T=4096 d=128, bf16),
     in the configuration the benchmark times: every row against the oracle."""
