@@ -39,8 +39,8 @@ BwdWs bwd_workspace_layout(const carve_dims_t* d) {
   const size_t nbh = (size_t)d->B * d->H;
   const size_t nch = (size_t)(d->T / d->L);
   size_t off = 0;
-  l.part = off;  off += align256(nbh * kUSplit * part_floats(d->R, d->Dk) * 4);
-  l.partV = off; off += align256(nbh * kVSplit * part_floats(d->R, d->Dk) * 4);
+  l.part = off;  off += align256(nbh * kMaxParamSplits * part_floats(d->R, d->Dk) * 4);
+  l.partV = off; off += align256(nbh * kMaxParamSplits * part_floats(d->R, d->Dk) * 4);
   // records of the full layer (2RP fold rows); the scalar-write records are smaller
   l.rec = off;   off += align256(nbh * nch * chunk_rec_bytes(d->dtype, d->Dk, d->L, 2 * round_rp(d->R), pick_nb(d)));
   l.sync = off;  off += align256(sync_ints(nbh, nch) * sizeof(int));
@@ -320,6 +320,7 @@ int bwd_impl(const carve_dims_t* d, const void* q, const void* k, const void* v,
   a.rec = wsb + wl.rec;
   a.opnd = wsb + wl.opnd;
   a.B = d->B; a.T = d->T; a.H = d->H; a.R = d->R; a.RP = RP; a.L = d->L; a.NB = nb;
+  a.splits = param_splits(d->B * d->H);
   a.wait_limit = g_wait_limit;
   int* sync = reinterpret_cast<int*>(wsb + wl.sync);
   prof_mark(stream);
@@ -337,7 +338,7 @@ int bwd_impl(const carve_dims_t* d, const void* q, const void* k, const void* v,
   // 4. fixed-order reductions of the partials
   const int nbh = d->B * d->H;
   const size_t RD = (size_t)d->R * d->Dk;
-  st = launch_param_reduce(a.part, nbh * kUSplit, a.partV, nbh * kVSplit, RD, dUb, sw ? nullptr : dUw, dVb,
+  st = launch_param_reduce(a.part, nbh * a.splits, a.partV, nbh * a.splits, RD, dUb, sw ? nullptr : dUw, dVb,
                            sw ? nullptr : dVw, stream);
   if (st) return st;
   prof_mark(stream);

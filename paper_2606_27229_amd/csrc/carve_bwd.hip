@@ -11,7 +11,7 @@ namespace carve {
 template <typename T, int D, int RP, bool SW>
 __global__ void __launch_bounds__(bwd_threads(D)) carve_bwd_param_kernel(BwdArgs a) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  const int nu = a.B * a.H * kUSplit;
+  const int nu = a.B * a.H * a.splits;
   if ((int)blockIdx.x < nu)
     uparam_item<T, D, RP, SW>(a, blockIdx.x, smem);
   else
@@ -227,7 +227,7 @@ static int launch_param_s(const BwdArgs& a, hipStream_t s) {
   if constexpr (lds > 64 * 1024) {
     return CARVE_ERR_UNSUPPORTED;   // only shapes the fused launch rejects first
   } else {
-    hipLaunchKernelGGL((carve_bwd_param_kernel<T, D, RP, SW>), dim3(a.B * a.H * (kUSplit + kVSplit)),
+    hipLaunchKernelGGL((carve_bwd_param_kernel<T, D, RP, SW>), dim3(a.B * a.H * 2 * a.splits),
                        dim3(bwd_threads(D)), lds, s, a);
     return hipGetLastError() == hipSuccess ? CARVE_OK : CARVE_ERR_HIP;
   }

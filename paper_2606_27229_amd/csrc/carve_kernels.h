@@ -292,13 +292,22 @@ struct BwdArgs {
   const void* rec;  // chunk records of the recompute (workspace)
   void* opnd;       // per-(b,h) operand quads of the parameters (workspace, adj_opnd_bytes each)
   int B, T, H, R, RP, L, NB;   // NB: 16-token tiles of a WY block of the backward
+  int splits;       // chunk and token splits of the parameter gradients per (batch, head)
   int wait_limit;   // polls of the adjoint's bounded wait for a chunk record
 };
 
-// token splits of the Vb / Vw gradient kernel and chunk splits of the [Ub; Uw]
-// gradient kernel (per (batch, head))
-constexpr int kVSplit = 16;
-constexpr int kUSplit = 16;
+// Splits per (batch, head) of the parameter-gradient partials: chunk splits of
+// d[Ub; Uw], token splits of dVb, dVw.  Each kind gets at least kParamItems
+// workgroups (two per compute unit, which keep the reads in flight since each
+// loads a step ahead); more splits than that only add partial records to write
+// and to sum: with 16 always, a training step at B*H = 128, T = 2048, d = 128
+// took 1337 us and now takes 1314; at B*H = 64, T = 4096 2182 and 2174 (up to
+// B*H = 32 nothing changes).
+constexpr int kMaxParamSplits = 16;
+constexpr int kParamItems = 512;
+__host__ __device__ constexpr int param_splits(int nbh) {
+  return nbh * kMaxParamSplits <= kParamItems ? kMaxParamSplits : (kParamItems + nbh - 1) / nbh;
+}
 
 // LDS layout of the adjoint for WY blocks of NB 16-token tiles (W = 16 NB
 // tokens).  dM holds the state gradient for the key side, then (from the

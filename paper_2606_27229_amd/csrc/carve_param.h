@@ -19,7 +19,7 @@ __host__ __device__ constexpr size_t uparam_lds() {
   return (sizeof(T) == 2 ? 2 : 1) * (size_t)D * (RF + 16 / sizeof(T)) * sizeof(T);
 }
 
-// item = (batch, head) * kUSplit + split; writes partial record `item`.  smem
+// item = (batch, head) * splits + split; writes partial record `item`.  smem
 // holds uparam_lds bytes; ends with a workgroup barrier.
 template <typename T, int D, int RP, bool SW>
 __device__ __forceinline__ void uparam_item(const BwdArgs& a, const int item, char* smem) {
@@ -38,13 +38,13 @@ __device__ __forceinline__ void uparam_item(const BwdArgs& a, const int item, ch
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int g = lane >> 4, c = lane & 15;
   const int Tn = a.T, L = a.L, R = a.R;
-  const int bh = item / kUSplit, split = item % kUSplit;
+  const int bh = item / a.splits, split = item % a.splits;
   const int nch = Tn / L;
   const ChunkRec cr = chunk_rec<T, D>(L, R2, a.NB);
   const char* recb = reinterpret_cast<const char*>(a.rec) + (size_t)bh * nch * cr.total;
   f32x4 acc[NRT];
   for (int rt = 0; rt < NRT; ++rt) acc[rt] = zero4();
-  const int per = (nch + kUSplit - 1) / kUSplit;
+  const int per = (nch + a.splits - 1) / a.splits;
   const int c0 = split * per, c1 = c0 + per < nch ? c0 + per : nch;
   // the next chunk's dF and state are loaded into registers while the current
   // one is multiplied: the kernel reads 96 KB per chunk (d = 128) for 64
@@ -94,7 +94,7 @@ __device__ __forceinline__ void uparam_item(const BwdArgs& a, const int item, ch
 // 16-byte vectors); the next step's rows are loaded into registers while the
 // current one is multiplied.
 // SW: the scalar write gate (dVb only; tau has the b columns only).
-// item = (batch, head) * kVSplit + split; writes partial record `item`.  smem
+// item = (batch, head) * splits + split; writes partial record `item`.  smem
 // holds vparam_lds bytes; ends with a workgroup barrier.
 template <typename T>
 __host__ __device__ constexpr int vparam_step_tokens() { return sizeof(T) == 2 ? 64 : 32; }
@@ -125,7 +125,7 @@ __device__ __forceinline__ void vparam_item(const BwdArgs& a, const int item, ch
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int g = lane >> 4, c = lane & 15;
   const int H = a.H, Tn = a.T, L = a.L, R = a.R;
-  const int bh = item / kVSplit, split = item % kVSplit;
+  const int bh = item / a.splits, split = item % a.splits;
   const int b = bh / H, h = bh % H;
   const int nch = Tn / L;
   const size_t bh0 = ((size_t)b * Tn * H + h) * D;
@@ -138,7 +138,7 @@ __device__ __forceinline__ void vparam_item(const BwdArgs& a, const int item, ch
   f32x4 accB[NRB], accW[NRB];
   for (int rt = 0; rt < NRB; ++rt) { accB[rt] = zero4(); accW[rt] = zero4(); }
   const int nblk = Tn / 16;
-  const int per = (nblk + kVSplit - 1) / kVSplit;
+  const int per = (nblk + a.splits - 1) / a.splits;
   const int blk0 = split * per, blk1 = blk0 + per < nblk ? blk0 + per : nblk;
   const int t_begin = 16 * blk0, t_end = 16 * blk1;
   u32x4 pb[NVT], pw[NVT], pt[NTT];
