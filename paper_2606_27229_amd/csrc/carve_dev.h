@@ -247,8 +247,13 @@ struct RecBuf {
   static constexpr int kAgent = 16;   // sc1
   template <typename V>
   __device__ __forceinline__ void st(unsigned off, unsigned lane_off, V v) const {
+    // 16 bytes: the whole offset in the vector operand.  With part of it in a
+    // scalar register the compiler takes the store data as read at issue and
+    // lets the next instruction overwrite a data register; under contention for the
+    // memory path the last lanes then stored the new value (seen in the erase
+    // gate of f32 layers with more than 512 workgroups on the card).
     if constexpr (sizeof(V) == 16)
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_g, v), r, (int)lane_off, (int)off, kAgent);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_g, v), r, (int)(off + lane_off), 0, kAgent);
     else if constexpr (sizeof(V) == 8)
       __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2_t, v), r, (int)lane_off, (int)off, kAgent);
     else
