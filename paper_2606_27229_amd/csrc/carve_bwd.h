@@ -75,10 +75,15 @@ namespace carve {
 // no more.  The bound is a kernel argument (BwdArgs::wait_limit,
 // kReadySpinLimit unless a test sets it) so that tests can make the wait give
 // up from the host while every kernel still runs to completion.
-// how many chunks ahead of the adjoint the recompute works, and the bound of
-// its wait for the adjoint's position (2^16 polls of a few hundred cycles:
-// milliseconds, far beyond a chunk's time)
-constexpr int kRecomputeLead = 4;
+// How many chunks ahead of the adjoint the recompute works: about 128 tokens.
+// Closer, the adjoint waits for records (one chunk of 64 tokens: T = 4096 step
+// 2605 us); further, more records lie in the caches between their two uses (2
+// chunks of 64 tokens 2086 us, 3 2110, 4 2152, 6 2223, 8 2226).  16-token chunks
+// take longer per token and want more of them (8: 372 us, 4: 389); chunks of
+// 128 tokens are two blocks (1: 1075 us, 2: 1028, 3 and 4: 1022).  The bound of
+// its wait for the adjoint's position: 2^16 polls of a few hundred cycles,
+// milliseconds, far beyond a chunk's time.
+constexpr int recompute_lead(int L) { return L > 64 ? 3 : 128 / L; }
 constexpr int kLeadSpinLimit = 1 << 16;
 
 // Compiler-only fence: keeps the LDS loads of one loop iteration from being
@@ -903,7 +908,7 @@ static int launch_fused_t(const FwdArgs& f, const BwdArgs& a, int* sync, int cus
     if (nrec < 1) nrec = 1;
     // pace the recompute only when every workgroup of the grid can be resident
     // at once (one per compute unit), so that the adjoints it follows run
-    const int lead = nrec + nbh <= cus ? kRecomputeLead : 0;
+    const int lead = nrec + nbh <= cus ? recompute_lead(a.L) : 0;
     hipLaunchKernelGGL(kern, dim3((unsigned)(nrec + nbh)), dim3(bwd_threads(D)), lds, stream, f, a, (int)nrec, sync,
                        lead);
     return hipGetLastError() == hipSuccess ? CARVE_OK : CARVE_ERR_HIP;
