@@ -154,31 +154,6 @@ __global__ void __launch_bounds__(fwd_threads(D)) carve_chain_fwd_kernel(FwdArgs
   const T* __restrict__ fl = GATED ? reinterpret_cast<const T*>(a.f) + bh0 : nullptr;
   T* __restrict__ o = reinterpret_cast<T*>(a.o) + bh0;
 
-  // ---- shared parameters ------------------------------------------------------
-  if (GATED)
-    for (int x = tid; x < D; x += NT) {
-      sGate[x] = -expf(a.A[h * D + x]);
-      sGate[D + x] = a.tau_f[h * D + x];
-    }
-  for (int x = tid; x < R2 * D; x += NT) {
-    const int rr = x / D, i = x % D;
-    float u = 0.0f;
-    if (rr < R) u = a.Ub[rr * D + i];
-    else if (!SW && rr >= RP && rr < RP + R) u = a.Uw[(rr - RP) * D + i];
-    sU[rr * LDD + (i ^ CARVE_QX(rr))] = (T)u;
-  }
-  // Vb / Vw operand quads, lane (g, c): V[16 w + c][16 ks + 4 g + e]
-  quad fVb[NRB], fVw[NRB];
-  for (int ks = 0; ks < NRB; ++ks) {
-    f32x4 tb, tw;
-    for (int e = 0; e < 4; ++e) {
-      const int r = 16 * ks + 4 * g + e;
-      tb[e] = r < R ? a.Vb[(16 * w + c) * R + r] : 0.0f;
-      tw[e] = (!SW && r < R) ? a.Vw[(16 * w + c) * R + r] : 0.0f;
-    }
-    fVb[ks] = Qd::cvt(tb);
-    fVw[ks] = Qd::cvt(tw);
-  }
   // identity operand, lane (g, c): I[4 g + e][c]
   quad fI;
   {
@@ -186,12 +161,6 @@ __global__ void __launch_bounds__(fwd_threads(D)) carve_chain_fwd_kernel(FwdArgs
     for (int e = 0; e < 4; ++e) t[e] = (4 * g + e == c) ? 1.0f : 0.0f;
     fI = Qd::cvt(t);
   }
-
-  // ---- state: St[jt][e] = S[v = 16 w + c][j = 16 jt + 4 g + e] ----------------
-  f32x4 St[NJT];
-  const size_t soff = (size_t)bh * D * D;
-  for (int jt = 0; jt < NJT; ++jt)
-    St[jt] = a.S0 ? gload4(a.S0 + soff + (16 * w + c) * D + 16 * jt + 4 * g) : zero4();
 
   // ---- prefetch registers ---------------------------------------------------------
   // q, k, bx: whole rows, 16 bytes per lane (coalesced), staged through LDS;
@@ -299,6 +268,24 @@ __global__ void __launch_bounds__(fwd_threads(D)) carve_chain_fwd_kernel(FwdArgs
   CARVE_PREFETCH_GATES(0);
   CARVE_PREFETCH_G(0);
   CARVE_PREFETCH_VW(0);
+
+  // ---- state: St[jt][e] = S[v = 16 w + c][j = 16 jt + 4 g + e] ----------------
+  f32x4 St[NJT];
+  const size_t soff = (size_t)bh * D * D;
+  for (int jt = 0; jt < NJT; ++jt)
+    St[jt] = a.S0 ? gload4(a.S0 + soff + (16 * w + c) * D + 16 * jt + 4 * g) : zero4();
+
+  // ---- shared parameters (behind the first block's loads) -----------------------
+  if (GATED)
+    for (int x = tid; x < D; x += NT) {
+      sGate[x] = -expf(a.A[h * D + x]);
+      sGate[D + x] = a.tau_f[h * D + x];
+    }
+  stage_U<T, D, RP, SW>(sU, a.Ub, a.Uw, R, tid);
+  // Vb / Vw operand quads, lane (g, c): V[16 w + c][16 ks + 4 g + e]
+  quad fVb[NRB], fVw[NRB];
+  load_V<T, RP>(fVb, a.Vb, R, 16 * w + c, g);
+  if constexpr (!SW) load_V<T, RP>(fVw, a.Vw, R, 16 * w + c, g);
 
   quad oq[NB];   // o of the previous block, lane (g, c): o[t = 16 bb + c][v = 16 w + 4 g + e]
   int oprev = -1;

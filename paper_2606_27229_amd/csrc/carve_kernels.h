@@ -56,6 +56,46 @@ struct RowTile {
     return Quad<T>::ld_tr_sw(t, LD, r0, c0, g, c);
   }
 };
+// The layer's parameters as matrix-core operands.  A workgroup takes them once,
+// at its start, where nothing hides a load: every load is issued before the
+// first use (rows and columns past R read a valid address and are zeroed by a
+// select, not skipped by a branch), so that they cost one memory latency
+// together with the first block's own loads (one 16-token chunk of 256 chains at
+// d = 128: 20.2 us with element loads one after another, 16.5 us now).
+// [Ub; 0; Uw; 0] (or [Ub; 0] with the scalar write gate) in the token dtype as a
+// RowTile; 4 D threads, 16 rows of 16-byte loads at a time
+template <typename T, int D, int RP, bool SW>
+__device__ __forceinline__ void stage_U(T* sU, const float* Ub, const float* Uw, int R, int tid) {
+  constexpr int N = (SW ? RP : 2 * RP) / 16;
+  const int r0 = tid / (D / 4), i = 4 * (tid % (D / 4));
+  f32x4 v[N];
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const int r = 16 * (u % (RP / 16)) + r0;
+    v[u] = gload4((u < RP / 16 ? Ub : Uw) + (r < R ? r : 0) * D + i);
+  }
+#pragma unroll
+  for (int u = 0; u < N; ++u) {
+    const int r = 16 * (u % (RP / 16)) + r0;
+    Quad<T>::st(sU + RowTile<T, D>::at(16 * u + r0, i & ~15, i & 12), Quad<T>::cvt(r < R ? v[u] : zero4()));
+  }
+}
+// operand quads of row `row` of V [rows][R], lane group g: V[row][16 ks + 4 g + e]
+template <typename T, int RP>
+__device__ __forceinline__ void load_V(typename Quad<T>::q (&f)[RP / 16], const float* V, int R, int row, int g) {
+  f32x4 t[RP / 16];
+#pragma unroll
+  for (int ks = 0; ks < RP / 16; ++ks)
+    for (int e = 0; e < 4; ++e) {
+      const int r = 16 * ks + 4 * g + e;
+      t[ks][e] = V[row * R + (r < R ? r : 0)];
+    }
+#pragma unroll
+  for (int ks = 0; ks < RP / 16; ++ks) {
+    for (int e = 0; e < 4; ++e) t[ks][e] = 16 * ks + 4 * g + e < R ? t[ks][e] : 0.0f;
+    f[ks] = Quad<T>::cvt(t[ks]);
+  }
+}
 // 16 x 16 coupling tiles (A, P, T, dA, dP), one after another: rows of 16
 // elements with qswz (bf16), or 20 (f32)
 template <typename T>

@@ -88,19 +88,6 @@ __device__ __forceinline__ u32x4_t unstage_vec(const T* src, int row, int k) {
   }
 }
 
-// [Ub; 0; Uw; 0] (or [Ub; 0]) in the token dtype as a RowTile
-template <typename T, int D, int RP, bool SW>
-__device__ __forceinline__ void stage_U(T* sU, const float* Ub, const float* Uw, int R, int tid, int NT) {
-  constexpr int RF = SW ? RP : 2 * RP;
-  for (int x = tid; x < RF * D; x += NT) {
-    const int rr = x / D, i = x % D;
-    float u = 0.0f;
-    if (rr < R) u = Ub[rr * D + i];
-    else if (!SW && rr >= RP && rr < RP + R) u = Uw[(rr - RP) * D + i];
-    sU[RowTile<T, D>::at(rr, i & ~15, i & 12) + (i & 3)] = (T)u;
-  }
-}
-
 // Recompute of the items first, first + stride, ... < nitems: item i is chunk
 // nch - 1 - i / (B*H) of (batch, head) i % (B*H) (latest chunks first, the order
 // in which the adjoint needs them).  sync: the synchronisation area (ready
@@ -163,20 +150,6 @@ __device__ __forceinline__ void rec_run(const FwdArgs& a, const int first, const
   const ChunkRec cr = chunk_rec<T, D>(L, RF, NB);
   const int rs = H * D;
 
-  // ---- shared parameters ------------------------------------------------------
-  stage_U<T, D, RP, SW>(sU, a.Ub, a.Uw, R, tid, NT);
-  // Vb / Vw operand quads: lane (g, c) holds V[16 w + c][16 ks + 4 g + e]
-  quad fVb[NRB], fVw[NRB];
-  for (int ks = 0; ks < NRB; ++ks) {
-    f32x4 tb, tw;
-    for (int e = 0; e < 4; ++e) {
-      const int r = 16 * ks + 4 * g + e;
-      tb[e] = r < R ? a.Vb[(16 * w + c) * R + r] : 0.0f;
-      tw[e] = (!SW && r < R) ? a.Vw[(16 * w + c) * R + r] : 0.0f;
-    }
-    fVb[ks] = Qd::cvt(tb);
-    fVw[ks] = Qd::cvt(tw);
-  }
 #define CARVE_FI() Qd::cvt(f32x4{4 * g == c ? 1.0f : 0.0f, 4 * g + 1 == c ? 1.0f : 0.0f, \
                                  4 * g + 2 == c ? 1.0f : 0.0f, 4 * g + 3 == c ? 1.0f : 0.0f})
 
@@ -240,6 +213,12 @@ __device__ __forceinline__ void rec_run(const FwdArgs& a, const int first, const
     CARVE_REC_PRE_V(bh, t0);
     CARVE_REC_PRE_G(bh, t0);
   }
+  // ---- shared parameters (behind the first block's loads) -----------------------
+  stage_U<T, D, RP, SW>(sU, a.Ub, a.Uw, R, tid);
+  // Vb / Vw operand quads: lane (g, c) holds V[16 w + c][16 ks + 4 g + e]
+  quad fVb[NRB], fVw[NRB];
+  load_V<T, RP>(fVb, a.Vb, R, 16 * w + c, g);
+  if constexpr (!SW) load_V<T, RP>(fVw, a.Vw, R, 16 * w + c, g);
   int* pending = nullptr;   // ready flag of the previous item, raised once its stores are complete
   int pending_val = 0;
 
