@@ -59,9 +59,10 @@
  *     each 16-token tile's range, with the products across tiles formed from
  *     operands no larger than the raw token values.  The sum of l over every
  *     16-token tile must stay above about -150 (-170 where a block is a
- *     single tile).  The backward evaluates 16-token blocks relative to the
- *     middle of their range, with factors up to e^{|sum of l over the block|
- *     / 2}, so each such block must sum above about -170.
+ *     single tile).  The backward evaluates blocks of up to 64 tokens
+ *     relative to the middle of their range, 16-token tile by tile where some
+ *     channel sums below -160 over the block, with factors up to e^{|sum of l|
+ *     / 2}, so each 16-token tile must sum above about -170.
  */
 #ifndef CARVE_H
 #define CARVE_H

@@ -191,28 +191,6 @@ template <typename T>
 __device__ __forceinline__ int qswz(int r) {
   return sizeof(T) == 2 ? ((r >> 2) & 3) << 2 : 0;
 }
-// The same three patterns on unpadded 256-byte bf16 rows (128 elements, 32
-// quads): quad q of row r at quad q ^ hq(r mod 16), hq linear over the bits of
-// r with images 4, 8, 17, 2.  hq mod 16 is a bijection of the 16 rows (writes),
-// and {1, 2, 4, 8, 17} is a basis of the quad index (both reads).
-// hswz128(r): the element-index XOR of row r.
-__device__ __forceinline__ int hswz128(int r) {
-  return (((r & 1) ? 4 : 0) ^ ((r & 2) ? 8 : 0) ^ ((r & 4) ? 17 : 0) ^ ((r & 8) ? 2 : 0)) << 2;
-}
-// Transposing read (rows r0 + 4 g + c / 4, columns c0 + 4 (c % 4), r0 a
-// multiple of 16) of a tile laid out with hswz128 (SXH: rows of LD = 128
-// elements; sxo = the lane's offset of row 4 g + c / 4 with its swizzle term,
-// computed once), or of a plain padded tile.
-template <bool SXH, typename T, int LD>
-__device__ __forceinline__ typename Quad<T>::q ld_sx_tile(const T* buf, int r0, int sxo, int c0, int g, int c) {
-  if constexpr (SXH) return Quad<T>::ld_tr_at(buf + r0 * LD + sxo);
-  else return Quad<T>::ld_tr(buf, LD, r0, c0, g, c);
-}
-// sxo of ld_sx_tile for the column block c0
-__device__ __forceinline__ int sx_lane_offset(int c0, int g, int c) {
-  const int r = 4 * g + (c >> 2);
-  return r * 128 + ((c0 + 4 * (c & 3)) ^ hswz128(r));
-}
 
 // global 4-element vector of the token dtype <-> f32x4
 __device__ __forceinline__ f32x4 gload4(const bf16_t* p) {
@@ -321,34 +299,6 @@ __device__ __forceinline__ f32x4 zero4() {
 template <typename T>
 __device__ __forceinline__ T to_t(float x) { return (T)x; }
 
-template <typename T>
-__device__ __forceinline__ float to_f(T x) { return (float)x; }
-
-// ---- result-tile stores ----------------------------------------------------
-// Tile (rows r0.., cols c0..) of the C layout into a row-major buffer.
-template <typename T>
-__device__ __forceinline__ void store_tile(T* buf, int ld, int r0, int c0, f32x4 v, int lane) {
-  const int g = lane >> 4, c = lane & 15;
-  T* p = buf + (size_t)(r0 + 4 * g) * ld + c0 + c;
-  p[0] = (T)v[0];
-  p[ld] = (T)v[1];
-  p[2 * ld] = (T)v[2];
-  p[3 * ld] = (T)v[3];
-}
-
-// Tile stored transposed: element (row, col) goes to buf[col * ld + row]; the
-// four rows a lane holds are contiguous.
-__device__ __forceinline__ void store_tile_t(bf16_t* buf, int ld, int r0, int c0, f32x4 v, int lane) {
-  const int g = lane >> 4, c = lane & 15;
-  bf16x4 o;
-  o[0] = (bf16_t)v[0]; o[1] = (bf16_t)v[1]; o[2] = (bf16_t)v[2]; o[3] = (bf16_t)v[3];
-  *reinterpret_cast<bf16x4*>(buf + (size_t)(c0 + c) * ld + r0 + 4 * g) = o;
-}
-__device__ __forceinline__ void store_tile_t(float* buf, int ld, int r0, int c0, f32x4 v, int lane) {
-  const int g = lane >> 4, c = lane & 15;
-  *reinterpret_cast<f32x4*>(buf + (size_t)(c0 + c) * ld + r0 + 4 * g) = v;
-}
-
 // ---- elementwise math (f32, hardware exp2/log2/rcp) -----------------------
 __device__ __forceinline__ float fast_exp(float x) { return __expf(x); }
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
@@ -370,10 +320,6 @@ __device__ __forceinline__ float softplus2_f(float z) {
 // natural log of x in [1, 2]: the hardware log2 and one product (no range
 // reduction or denormal scaling is needed there)
 __device__ __forceinline__ float log_1to2(float x) { return __builtin_amdgcn_logf(x) * 0.693147180559945f; }
-// log(1 + e^z) without overflow
-__device__ __forceinline__ float softplus_f(float z) {
-  return fmaxf(z, 0.0f) + log_1to2(1.0f + fast_exp(-fabsf(z)));
-}
 // softplus(z) = log(1 + e^z) and sigmoid(z) from one exponential
 __device__ __forceinline__ void softplus_sigmoid(float z, float& sp, float& sig) {
   const float e = fast_exp(-fabsf(z));
