@@ -61,7 +61,7 @@
  *     16-token tile must stay above about -150 (-170 where a block is a
  *     single tile).  The backward evaluates blocks of up to 64 tokens
  *     relative to the middle of their range, 16-token tile by tile where some
- *     channel sums below -160 over the block, with factors up to e^{|sum of l|
+ *     channel sums below -80 over the block, with factors up to e^{|sum of l|
  *     / 2}, so each 16-token tile must sum above about -170.
  */
 #ifndef CARVE_H

@@ -247,6 +247,14 @@ struct ChainLds {
 // log retention over the block stays above -kWideLog (factors up to
 // e^{kWideLog / 2}), per-tile references otherwise.
 constexpr float kWideLog = 160.0f;
+// The backward's bound is half of that (factors up to e^{kBwdWideLog / 2} =
+// 2e17): its state gradient and block start state meet these factors as bf16
+// operands, e^{rho} dS among them, and gradients are often small.  With 160,
+// gradients of 1e-6 lost their part through a channel that decays by 2.4 per
+// token (e^{-77} 1e-6 is below bf16's range): dk was wrong by 6.7 % (2-norm; with
+// blocks of 16 tokens 0.4 %).  Layers whose channels decay by up to one per
+// token stay on the one-reference evaluation.
+constexpr float kBwdWideLog = 80.0f;
 __host__ __device__ constexpr int fwd_tab_rows(int NB) {
   return NB == 1 ? 1 : 3 * NB + 1 + (NB - 1) * (NB - 2) / 2;
 }

@@ -32,7 +32,7 @@
 // the key operand, so that the adjoint has one rounded operand for A and for
 // the prediction.  No factor exceeds e^{|lam_end| / 2}.
 //
-// A block in which some key channel decays by more than e^{-kWideLog} is
+// A block in which some key channel decays by more than e^{-kBwdWideLog} is
 // evaluated tile by tile instead: lam, rho and the state run per 16-token tile,
 // and the adjoint walks the block's tiles as blocks of one tile.  The choice is
 // a vote of the workgroup and goes to the adjoint with the chunk's ready flag.
@@ -367,7 +367,7 @@ __device__ __forceinline__ void rec_run(const FwdArgs& a, const int first, const
       bool wide = false;
       if constexpr (NB > 1) {
         bool mine = false;
-        for (int i = 0; i < 4; ++i) mine = mine || row_bcast15(lam[NB - 1][i]) < -kWideLog * kLog2e;
+        for (int i = 0; i < 4; ++i) mine = mine || row_bcast15(lam[NB - 1][i]) < -kBwdWideLog * kLog2e;
         const bool wv_wide = __any(mine) != 0;
         if (lane == 0) sFlag[w] = wv_wide ? 1 : 0;
       }

@@ -2,7 +2,7 @@
 the CPU oracle's exact reverse mode.
 
 A block of up to 64 tokens takes one log-retention reference per key channel
-while every channel stays above -160 over the block, and is evaluated 16-token
+while every channel stays above -80 over the block, and is evaluated 16-token
 tile by tile otherwise.  Blocks of both kinds follow each other here in every
 order: first and last of the call, alternating, several in a row, and different
 kinds inside one 128-token chunk (two blocks), with 16-, 32- and 64-token
