@@ -455,24 +455,53 @@ __device__ __forceinline__ void rec_run(const FwdArgs& a, const int first, const
             acc = Qd::mma32(k0, k1, i0, i1, acc);     // Kh_{t = 4 g + e} . Ki_{s = c}
             accT = Qd::mma32(i0, i1, k0, k1, accT);   // Ki_{s = 4 g + e} . Kh_{t = c}
           }
-          // T = (I + A)^{-1} = (I + M)(I + M^2)(I + M^4)(I + M^8), M = -A (M^16 = 0)
-          f32x4 mB, mA, I4;   // M in the result layout (M[4g+e][c]) and transposed (M[c][4g+e])
-          for (int e = 0; e < 4; ++e) {
-            mB[e] = (c < 4 * g + e) ? -acc[e] : 0.0f;
-            mA[e] = (4 * g + e < c) ? -accT[e] : 0.0f;
-            I4[e] = (4 * g + e == c) ? 1.0f : 0.0f;
+          T* tt = sC + (NTP + NTA + i) * ST::N;
+          if constexpr (sizeof(T) == 4) {
+            // f32: T[c][s] = delta(c, s) - sum_{t > s} T[c][t] A[t][s], s = 15 .. 0,
+            // row c in lane c, from A^T parked in T's own place (one wave, whose
+            // LDS accesses are in order).  The product form below loses T to
+            // cancellation where the keys are alike: relative error 8e-5 for
+            // equal keys, 6e-8 by substitution (below bf16's rounding, but not
+            // below f32's).
+            f32x4 av;
+            for (int e = 0; e < 4; ++e) av[e] = (c < 4 * g + e) ? acc[e] : 0.0f;
+            Qd::st(tt + ST::at(c, 4 * g), av);   // A[4 g + e][c] in row c
+            asm volatile("" ::: "memory");
+            float x[16];
+#pragma unroll
+            for (int s = 15; s >= 0; --s) {
+              float acc0 = (s == c) ? 1.0f : 0.0f, acc1 = 0.0f;
+#pragma unroll
+              for (int t = s + 1; t < 16; ++t) {
+                if ((t - s) & 1) acc0 -= x[t] * tt[ST::at(s, t)];
+                else acc1 -= x[t] * tt[ST::at(s, t)];
+              }
+              x[s] = acc0 + acc1;
+            }
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+              if (g == k) Qd::st(tt + ST::at(c, 4 * k), f32x4{x[4 * k], x[4 * k + 1], x[4 * k + 2], x[4 * k + 3]});
+          } else {
+            // T = (I + A)^{-1} = (I + M)(I + M^2)(I + M^4)(I + M^8), M = -A (M^16 = 0)
+            f32x4 mB, mA, I4;   // M in the result layout (M[4g+e][c]) and transposed (M[c][4g+e])
+            for (int e = 0; e < 4; ++e) {
+              mB[e] = (c < 4 * g + e) ? -acc[e] : 0.0f;
+              mA[e] = (4 * g + e < c) ? -accT[e] : 0.0f;
+              I4[e] = (4 * g + e == c) ? 1.0f : 0.0f;
+            }
+            const f32x4 M2 = Qf::mma16(mA, mB, zero4());
+            const f32x4 M2t = Qf::mma16(mB, mA, zero4());
+            const f32x4 M4 = Qf::mma16(M2t, M2, zero4());
+            const f32x4 M4t = Qf::mma16(M2, M2t, zero4());
+            // the factors commute; formed transposed (rows s, columns t), so that
+            // a lane's four elements are one row quad of T: T[c][4g..4g+3]
+            const f32x4 M8t = Qf::mma16(M4, M4t, zero4());
+            const f32x4 X1 = Qf::mma16(M4 + I4, M8t + I4, zero4());
+            const f32x4 X2 = Qf::mma16(M2 + I4, X1, zero4());
+            const f32x4 Tt = Qf::mma16(mB + I4, X2, zero4());
+            Qd::st(tt + ST::at(c, 4 * g), Qd::cvt(Tt));
           }
-          const f32x4 M2 = Qf::mma16(mA, mB, zero4());
-          const f32x4 M2t = Qf::mma16(mB, mA, zero4());
-          const f32x4 M4 = Qf::mma16(M2t, M2, zero4());
-          const f32x4 M4t = Qf::mma16(M2, M2t, zero4());
-          // the factors commute; formed transposed (rows s, columns t), so that
-          // a lane's four elements are one row quad of T: T[c][4g..4g+3]
-          const f32x4 M8t = Qf::mma16(M4, M4t, zero4());
-          const f32x4 X1 = Qf::mma16(M4 + I4, M8t + I4, zero4());
-          const f32x4 X2 = Qf::mma16(M2 + I4, X1, zero4());
-          const f32x4 Tt = Qf::mma16(mB + I4, X2, zero4());
-          Qd::st(sC + (NTP + NTA + i) * ST::N + ST::at(c, 4 * g), Qd::cvt(Tt));
         }
       }
       if (NOW == NW || w < NOW) {
