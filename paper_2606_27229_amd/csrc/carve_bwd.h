@@ -332,7 +332,7 @@ struct Adjoint {
       for (int i = NB - 1; i >= 0; --i) {
         f32x4 r = du[i];
         for (int j = i + 1; j < NB; ++j) r = Qd::mma16(ST::tr(sC + (NTP + tri_strict(j, i)) * ST::N, g, c), xq[j], r);
-        dR[i] = Qd::mma16(ST::tr(sC + (NTP + NTA + i) * ST::N, g, c), Qd::cvt(r), zero4());
+        dR[i] = ST::apply_T(ST::tr(sC + (NTP + NTA + i) * ST::N, g, c), r);
         xq[i] = Qd::cvt(dR[i]);
         nq[i] = Qd::cvt(-dR[i]);
         // exchange: token rows of -dR for the products over the value axis

@@ -106,6 +106,14 @@ struct SmallTile {
   static __device__ __forceinline__ typename Quad<T>::q tr(const T* t, int g, int c) {
     return Quad<T>::ld_tr_sw(t, LD, 0, 0, g, c);
   }
+  // T x (or T^T x) for a unit triangular T, from its tile's operand quads: bf16
+  // tiles hold T - I and x enters once more in f32, so that its rounding to an
+  // operand meets T - I only (2-norm errors against 64 bits, layer with B = 4,
+  // H = 16, T = 4096, d = 128: dv 3.74e-3 with T itself, 3.34e-3 now, dk 3.74e-3
+  // and 3.37e-3, dg 3.74e-3 and 3.40e-3); f32 tiles hold T
+  static __device__ __forceinline__ f32x4 apply_T(typename Quad<T>::q t, f32x4 x) {
+    return Quad<T>::mma16(t, Quad<T>::cvt(x), sizeof(T) == 2 ? x : f32x4{0.0f, 0.0f, 0.0f, 0.0f});
+  }
 };
 
 // Lower-triangular 16-token tile pairs (i, j) of a block of NB tiles, row-major:
@@ -127,7 +135,7 @@ __host__ __device__ constexpr int tiles_all(int NB) { return tiles_p(NB) + tiles
 //   Tau  [L][RF]                tanh(q F^T), plain rows
 //   K    per block [3][16 NB] rows, tile images: beta Kt, Qt, Ki
 //   U    per block [16 NB] rows, tile image: u
-//   C    per block tiles_all(NB) coupling tiles, tile images: P, -A, T
+//   C    per block tiles_all(NB) coupling tiles, tile images: P, -A, T (bf16: T - I)
 //   S    [L/16][D/16][NT] quads S'[16 vt + 4 g + e][16 w + c], the block start
 //                               state times the block's reference e^{rho}: entry
 //                               NB m of block m, or (per-tile evaluation) entry

@@ -499,7 +499,8 @@ __device__ __forceinline__ void rec_run(const FwdArgs& a, const int first, const
             const f32x4 M8t = Qf::mma16(M4, M4t, zero4());
             const f32x4 X1 = Qf::mma16(M4 + I4, M8t + I4, zero4());
             const f32x4 X2 = Qf::mma16(M2 + I4, X1, zero4());
-            const f32x4 Tt = Qf::mma16(mB + I4, X2, zero4());
+            f32x4 Tt = Qf::mma16(mB + I4, X2, zero4());
+            for (int e = 0; e < 4; ++e) Tt[e] = 4 * g + e < c ? Tt[e] : 0.0f;
             Qd::st(tt + ST::at(c, 4 * g), Qd::cvt(Tt));
           }
         }
@@ -546,7 +547,7 @@ __device__ __forceinline__ void rec_run(const FwdArgs& a, const int first, const
           f32x4 r = wv[i];
           for (int j = 0; j < i; ++j)
             r = Qd::mma16(Qd::ld(sC + (NTP + tri_strict(i, j)) * ST::N + ST::at(c, 4 * g)), uq[j], r);
-          uq[i] = Qd::cvt(Qd::mma16(Qd::ld(sC + (NTP + NTA + i) * ST::N + ST::at(c, 4 * g)), Qd::cvt(r), zero4()));
+          uq[i] = Qd::cvt(ST::apply_T(Qd::ld(sC + (NTP + NTA + i) * ST::N + ST::at(c, 4 * g)), r));
         }
         for (int vt = 0; vt < NJT; ++vt) rec.st(cr.S + (m * NB * NJT + vt) * NT * QB, tid * QB, RT::tr(sX, 16 * vt, 16 * w, g, c));
         if (!last) {
@@ -573,7 +574,7 @@ __device__ __forceinline__ void rec_run(const FwdArgs& a, const int first, const
             wv[bb] -= xk;
             __syncthreads();
           }
-          uq[bb] = Qd::cvt(Qd::mma16(Qd::ld(sC + (NTP + NTA + bb) * ST::N + ST::at(c, 4 * g)), Qd::cvt(wv[bb]), zero4()));
+          uq[bb] = Qd::cvt(ST::apply_T(Qd::ld(sC + (NTP + NTA + bb) * ST::N + ST::at(c, 4 * g)), wv[bb]));
           for (int vt = 0; vt < NJT; ++vt) rec.st(cr.S + ((m * NB + bb) * NJT + vt) * NT * QB, tid * QB, RT::tr(sX, 16 * vt, 16 * w, g, c));
           for (int jt = 0; jt < NJT; ++jt) {
             const f32x4 er = *reinterpret_cast<const f32x4*>(sGam + bb * D + 16 * jt + 4 * g);
