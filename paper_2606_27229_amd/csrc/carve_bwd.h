@@ -316,9 +316,7 @@ struct Adjoint {
       for (int tt = 0; tt < NB; ++tt) dOq[tt] = RT::tr(sdO, 16 * tt, 16 * w, g, c);
       f32x4 du[NB];
       for (int tt = 0; tt < NB; ++tt) {
-        // (two chains, added at the end: a K16 step accumulating directly on the
-        // result of a K32 step read it too early here, with wrong values in the
-        // first two rows of every quad)
+        // (two chains, added at the end: mma16 never accumulates on a mma32 result)
         f32x4 dp = zero4();
         for (int i = tt; i < NB; ++i) dp = Qd::mma16(ST::tr(sC + tri_incl(i, tt) * ST::N, g, c), dOq[i], dp);
         du[tt] = zero4();

@@ -95,6 +95,13 @@ struct Mma<float> {
 // 4-element quads either along a row ("natural": lane c reads row c) or across
 // four rows ("transposed": lane c reads column c), the latter with the gfx950
 // transposing LDS read for 16-bit data.
+//
+// One accumulator takes either K16 or K32 steps: a bf16 mma16 directly on the
+// result of a mma32, or the other way round, gets no wait states from the
+// compiler and the card then returns wrong values (K16 on K32: rows 0 and 1 of
+// every quad, K32 on K16: rows 2 and 3; measured, every time).  Chains of both
+// kinds are added at the end, or lie a barrier apart; tests/test_mfma_hazards.py
+// checks the distances in the compiled library.
 template <typename T>
 struct Quad;
 

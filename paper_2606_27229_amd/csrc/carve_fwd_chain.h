@@ -675,8 +675,6 @@ __global__ void __launch_bounds__(fwd_threads(D)) carve_chain_fwd_kernel(FwdArgs
             acc1 = Qd::mma32(Qd::ld(ar1 + 32 * jp), Qd::ld(ar1 + 32 * jp + 16), Qd::ld(br1 + 32 * jp),
                              Qd::ld(br1 + 32 * jp + 16), acc1);
           }
-          // (both results leave the matrix pipe before put_tile's branch)
-          asm volatile("" : "+v"(acc0), "+v"(acc1));
           put_tile(x0, i0, j0, acc0);
           put_tile(x1, i1, j1, acc1);
         }
@@ -707,7 +705,6 @@ __global__ void __launch_bounds__(fwd_threads(D)) carve_chain_fwd_kernel(FwdArgs
               acc = Qd::mma32(Qd::ld(ar + 32 * jp), Qd::ld(ar + 32 * jp + 16), Qd::ld(br + 32 * jp),
                               Qd::ld(br + 32 * jp + 16), acc);
           }
-          asm volatile("" : "+v"(acc));
           put_tile(x, i, j, acc);
         }
       }
