@@ -66,25 +66,14 @@
 
 namespace carve {
 
-// Bound of the ready-flag wait: 2^20 polls (each a few device-scope
-// loads and a short sleep; about a second in all).  A chunk is recomputed in
-// tens of microseconds by a workgroup that never waits for long, so the bound
-// is not reached in a correct launch; if it is, every wave poisons its state
-// gradient with NaN (every gradient of earlier tokens then comes out NaN), the
-// wait-timeout word of the synchronisation area is set and the workgroup waits
-// no more.  The bound is a kernel argument (BwdArgs::wait_limit,
-// kReadySpinLimit unless a test sets it) so that tests can make the wait give
-// up from the host while every kernel still runs to completion.
-// How many chunks ahead of the adjoint the recompute works: about 128 tokens.
-// Closer, the adjoint waits for records (one chunk of 64 tokens: T = 4096 step
-// 2605 us); further, more records lie in the caches between their two uses (2
-// chunks of 64 tokens 2086 us, 3 2110, 4 2152, 6 2223, 8 2226).  16-token chunks
-// take longer per token and want more of them (8: 372 us, 4: 389); chunks of
-// 128 tokens are two blocks (1: 1075 us, 2: 1028, 3 and 4: 1022).  The bound of
-// its wait for the adjoint's position: 2^16 polls of a few hundred cycles,
-// milliseconds, far beyond a chunk's time.
+// How many chunks ahead of the adjoint the recompute works: 128 tokens in chunks
+// of up to 64, 384 in chunks of 128.  Closer, the adjoint waits for records (one
+// chunk of 64 tokens: T = 4096 step 2605 us); further, more records lie in the
+// caches between their two uses (2 chunks of 64 tokens 2086 us, 3 2110, 4 2152,
+// 6 2223, 8 2226).  16-token chunks take longer per token and want more of them
+// (8: 372 us, 4: 389); chunks of 128 tokens are two blocks (1: 1075 us, 2: 1028,
+// 3 and 4: 1022).
 constexpr int recompute_lead(int L) { return L > 64 ? 3 : 128 / L; }
-constexpr int kLeadSpinLimit = 1 << 16;
 
 // Compiler-only fence: keeps the LDS loads of one loop iteration from being
 // hoisted above the previous one (bounds the number of live operand registers).
@@ -709,6 +698,8 @@ struct Adjoint {
   }
 
   __device__ __forceinline__ void run() {
+    // running: the recompute may follow this adjoint
+    if (tid == 0) __hip_atomic_store(pos, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // operand quads of the parameters, written once to this workgroup's part of
     // the workspace in thread order and read back where they are used (each
     // thread its own; from cache): V^T of the wave's dtau tiles (lane (g, c):
@@ -756,7 +747,7 @@ struct Adjoint {
     for (int ch = nch - 1; ch >= 0; --ch) {
       const int ctl = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(smem + lay.Ctl)[0]);
       const int wide = ctl > 0 ? ctl : 0;
-      if (tid == 0) __hip_atomic_store(pos, nch - ch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (tid == 0) __hip_atomic_store(pos, 1 + nch - ch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       f32x4 dF[NRT];
       quad fU[NRT];
 #pragma unroll 1
@@ -855,9 +846,9 @@ struct Adjoint {
 // for a bounded time, so every flag an adjoint workgroup waits for is raised in
 // finite time whatever order the hardware dispatches the grid in.  With lead >
 // 0 a recompute workgroup starts a chunk only once the adjoint of its (batch,
-// head) has started the chunk lead places before it (a bounded wait): records
-// are then written shortly before they are read, and the recompute's stores do
-// not all come at once.
+// head) has started the chunk lead places before it (a bounded wait,
+// kPresentSpinLimit and kLeadSpinLimit): records are then written shortly before
+// they are read, and the recompute's stores do not all come at once.
 template <typename T, int D, int RP, int VAR, int NB>
 __global__ void __launch_bounds__(bwd_threads(D)) __attribute__((amdgpu_waves_per_eu(1, 2)))
 carve_bwd_fused_kernel(FwdArgs f, BwdArgs a, int nrec, int* sync, int lead) {
@@ -870,7 +861,7 @@ carve_bwd_fused_kernel(FwdArgs f, BwdArgs a, int nrec, int* sync, int lead) {
   const int ticket = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(smem)[0]);
   __syncthreads();
   if (ticket < nrec) {
-    rec_run<T, D, RP, VAR, NB>(f, ticket, nrec, sync, lead, kLeadSpinLimit, smem);
+    rec_run<T, D, RP, VAR, NB>(f, ticket, nrec, sync, lead, smem);
   } else {
     const int bh = ticket - nrec;
     Adjoint<T, D, RP, VAR, NB>(a, bh, smem, sync, sync + sync_timeout_word(nbh, nch), sync + sync_adjoint_pos(nbh, nch) + bh)
@@ -905,7 +896,8 @@ static int launch_fused_t(const FwdArgs& f, const BwdArgs& a, int* sync, int cus
     if (nrec > nitems) nrec = nitems;
     if (nrec < 1) nrec = 1;
     // pace the recompute only when every workgroup of the grid can be resident
-    // at once (one per compute unit), so that the adjoints it follows run
+    // at once (one per compute unit), so that the adjoints it follows run unless
+    // other work holds compute units
     const int lead = nrec + nbh <= cus ? recompute_lead(a.L) : 0;
     hipLaunchKernelGGL(kern, dim3((unsigned)(nrec + nbh)), dim3(bwd_threads(D)), lds, stream, f, a, (int)nrec, sync,
                        lead);

@@ -444,13 +444,21 @@ size_t chunk_rec_bytes(int dtype, int D, int L, int RF, int NB);
 // ints of the synchronisation area: one ready flag per chunk, the ticket
 // counter that assigns the workgroup roles, the wait-timeout word (nonzero once
 // an adjoint wave's bounded wait for a record ran out), padding, then per
-// (batch, head) the adjoint's position (chunks it has started, counted from the
-// last), which paces the recompute
+// (batch, head) the adjoint's position, which paces the recompute: 0 before it
+// runs, then 1 + the chunks it has started (counted from the last)
 __host__ __device__ constexpr size_t sync_ints(size_t nbh, size_t nch) { return nbh * nch + 4 + nbh; }
 __host__ __device__ constexpr size_t sync_ticket(size_t nbh, size_t nch) { return nbh * nch; }
 __host__ __device__ constexpr size_t sync_timeout_word(size_t nbh, size_t nch) { return nbh * nch + 1; }
 __host__ __device__ constexpr size_t sync_adjoint_pos(size_t nbh, size_t nch) { return nbh * nch + 4; }
-// default bound of that wait, in polls (carve_bwd.h)
+// Bound of the adjoint's wait for a chunk's flag: 2^20 polls (each a device-scope
+// load and a short sleep; about a second in all).  A chunk is recomputed in tens
+// of microseconds, by a workgroup that waits for at most kLeadSpinLimit polls of
+// its own once, so the bound is not reached in a correct launch; if it is, every
+// wave poisons its state gradient with NaN (every gradient of earlier tokens
+// then comes out NaN), the wait-timeout word is set and the workgroup waits no
+// more.  It is a kernel argument (BwdArgs::wait_limit, this unless a test sets
+// it) so that tests can make the wait give up from the host while every kernel
+// still runs to completion.
 constexpr int kReadySpinLimit = 1 << 20;
 // d[Ub; Uw] over chunk splits and dVb, dVw over token splits (carve_param.h),
 // one launch; sw: the scalar write gate (dVb, dUb only; the records hold RP

@@ -92,11 +92,21 @@ __device__ __forceinline__ u32x4_t unstage_vec(const T* src, int row, int k) {
 // nch - 1 - i / (B*H) of (batch, head) i % (B*H) (latest chunks first, the order
 // in which the adjoint needs them).  sync: the synchronisation area (ready
 // flags, adjoint positions); with lead > 0 an item is started only once the
-// adjoint of its (batch, head) has started the chunk lead places before it (a
-// bounded wait).  smem: the workgroup's dynamic LDS (RecLds layout).
+// adjoint of its (batch, head) has started the chunk lead places before it.  A
+// workgroup whose wait runs out follows no adjoint any more, so that waiting
+// costs it one bound in all and not one per item (other streams' work may hold
+// the compute units that the adjoints would take).
+// smem: the workgroup's dynamic LDS (RecLds layout).
+// Bounds of that wait, in polls of a few hundred cycles: for an adjoint that has
+// not begun (2^8, about 100 us, many times a launch's own spread), and for one
+// that has (2^16, tens of milliseconds; it waits for nothing but other chunks'
+// recompute).
+constexpr int kPresentSpinLimit = 1 << 8;
+constexpr int kLeadSpinLimit = 1 << 16;
+
 template <typename T, int D, int RP, int VAR, int NB>
-__device__ __forceinline__ void rec_run(const FwdArgs& a, const int first, const int stride, int* sync, const int lead,
-                                        const int spin_limit, char* smem) {
+__device__ __forceinline__ void rec_run(const FwdArgs& a, const int first, const int stride, int* sync, int lead,
+                                        char* smem) {
   typedef Quad<T> Qd;
   typedef typename Qd::q quad;
   typedef RowTile<T, D> RT;
@@ -238,12 +248,17 @@ __device__ __forceinline__ void rec_run(const FwdArgs& a, const int first, const
       }
       if (tid == 0) {
         const int* p = sync + sync_adjoint_pos(nbh, nch) + bh;
-        for (int n = 0; n < spin_limit; ++n) {
-          if (__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > row - lead) break;
+        int go = 0;
+        for (int n = 0; n < kLeadSpinLimit; ++n) {
+          const int v = __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          go = v > 1 + row - lead;
+          if (go || (v == 0 && n >= kPresentSpinLimit)) break;
           __builtin_amdgcn_s_sleep(4);
         }
+        sFlag[15] = go;
       }
       __syncthreads();
+      if (__builtin_amdgcn_readfirstlane(sFlag[15]) == 0) lead = 0;
     }
     int wide_bits = 0;
 #pragma unroll 1
