@@ -52,7 +52,12 @@
 // and at the chunk start the folded read-out closes the chain ("glue"):
 //   dS += [Ub; Uw]^T dF,   d[Ub; Uw] += dF S_hat^T.
 // A block that the recompute evaluated tile by tile (carve_rec.h) is walked as
-// NB blocks of one tile.
+// NB blocks of one tile.  Its images, coupling tiles and dO rows come to LDS with
+// those of any other block, loaded while the block before runs, and each tile
+// takes its own rows there; what a tile reads from the record beside them is
+// loaded during the tile before (at B = 4, H = 16, T = 4096, d = 128 with every
+// block of this kind the backward takes 1.92 ms, 2.77 with each tile loaded when
+// its turn came; 1.40 with none).
 // With the scalar write gate (kVarScalarW; w_t = sigmoid(wx_t) on every value
 // channel, no write-side content) the fold is Ub S_hat alone, there is no
 // dtau_w, and the gradient of the token's write logit is the sum over the
@@ -206,19 +211,50 @@ struct Adjoint {
       p.v[tt] = rc.template ld<quad>(cr.V + (m * NBK + tt) * NT * QB, tid * QB);
     }
   }
+  // what one tile of a block evaluated tile by tile takes from the record beside
+  // the images
+  struct TilePre {
+    quad S[NJT], sig, q, v, tau[NVS];
+    f32x4 E, wg, gam;
+    quad FT[NRT];   // of the chunk
+  };
+  __device__ __forceinline__ void load_tile(TilePre& t, int ch, int tile) const {
+    const RecBuf rc(rec_of(ch), cr.total);
+    t.gam = rc.template ld<f32x4>(cr.Gam + tile * D * 4, 16 * vec<D / 4>(0));
+    t.v = rc.template ld<quad>(cr.V + tile * NT * QB, tid * QB);
+    if constexpr (!SW) t.wg = rc.template ld<f32x4>(cr.W + tile * NT * 16, tid * 16);
+    for (int vt = 0; vt < NJT; ++vt) t.S[vt] = rc.template ld<quad>(cr.S + (tile * NJT + vt) * NT * QB, tid * QB);
+    t.E = rc.template ld<f32x4>(cr.E + tile * NT * 16, tid * 16);
+    t.sig = rc.template ld<quad>(cr.Sig + tile * NT * QB, tid * QB);
+    t.q = rc.template ld<quad>(cr.Q + tile * NT * QB, tid * QB);
+    for (int k = 0; k < NVS; ++k) t.tau[k] = load_tau(rc, tile, w % NRW + k * NRW);
+  }
+  __device__ __forceinline__ quad load_tau(const RecBuf& rc, int tile, int rt) const {
+    return rc.template ld<quad>(cr.Tau + (16 * tile * RF + 16 * rt) * (int)sizeof(T), (c * RF + 4 * g) * (int)sizeof(T));
+  }
+  // operands of dF, dq and the glue: [Ub; Uw] and F^T of the chunk
+  __device__ __forceinline__ void load_fold(quad (&fU)[NRT], quad (&FT)[NRT], int ch) const {
+    const RecBuf rc(rec_of(ch), cr.total);
+    for (int rt = 0; rt < NRT; ++rt) fU[rt] = Qd::ld(opnd + ((size_t)(NVS * NJT + rt) * NT + tid) * 4);
+    for (int rt = 0; rt < NRT; ++rt) FT[rt] = rc.template ld<quad>(cr.FT + rt * NT * QB, tid * QB);
+  }
   // registers -> LDS
+  __device__ __forceinline__ void put_gam(f32x4 gam) const {
+    *reinterpret_cast<f32x4*>(smem + lay.Gam + 16 * vec<D / 4>(0)) = gam;
+  }
   __device__ __forceinline__ void put_tiles(const Pre& p) const {
     u32x4_t* dk = reinterpret_cast<u32x4_t*>(smem + lay.Kt);
     for (int u = 0; u < NKV; ++u) dk[vec<3 * NVK>(u)] = p.k[u];
     u32x4_t* dc = reinterpret_cast<u32x4_t*>(smem + lay.C);
     for (int u = 0; u < NCV; ++u) dc[vec<NVC>(u)] = p.cc[u];
-    *reinterpret_cast<f32x4*>(smem + lay.Gam + 16 * vec<D / 4>(0)) = p.gam;
+    put_gam(p.gam);
     ldf(lay.Beta)[vec<W>(0)] = p.beta;
     if constexpr (SW) ldf(lay.Ws)[vec<W>(0)] = p.ws;
   }
-  __device__ __forceinline__ void load_scalars(Pre& p, int ch, int m) const {
+  // (wide: a block evaluated tile by tile; its last tile's reference comes first)
+  __device__ __forceinline__ void load_scalars(Pre& p, int ch, int m, bool wide) const {
     const RecBuf rc(rec_of(ch), cr.total);
-    p.gam = rc.template ld<f32x4>(cr.Gam + m * NBK * D * 4, 16 * vec<D / 4>(0));
+    p.gam = rc.template ld<f32x4>(cr.Gam + (m * NBK + (wide ? NBK - 1 : 0)) * D * 4, 16 * vec<D / 4>(0));
     p.beta = rc.template ld<float>(cr.Beta + m * W * 4, 4 * vec<W>(0));
     if constexpr (SW) p.ws = rc.template ld<float>(cr.Beta + (L + m * W) * 4, 4 * vec<W>(0));
   }
@@ -230,68 +266,51 @@ struct Adjoint {
     }
   }
 
-  // One tile of a block evaluated tile by tile: its rows of the images, its P
-  // and T tiles and its dO rows straight into LDS (the layout of a block of one
-  // tile), its gates into p.
-  __device__ __forceinline__ void load_tile_direct(Pre& p, int ch, int m, int i) const {
-    const RecBuf rc(rec_of(ch), cr.total);
-    constexpr int NV1 = (int)(image_bytes<T, D>(16) / 16);
-    for (int y = 0; y < 4; ++y) {
-      const unsigned src = (y < 3 ? cr.K + (3 * m + y) * image_bytes<T, D>(W) : cr.U + m * image_bytes<T, D>(W)) + i * image_bytes<T, D>(16);
-      const size_t dst = y == 0 ? lay.Kt : y == 1 ? lay.Qt : y == 2 ? lay.Ki : lay.U;
-      for (int x = tid; x < NV1; x += NT)
-        reinterpret_cast<u32x4_t*>(smem + dst)[x] = rc.template ld<u32x4_t>(src, 16 * x);
-    }
-    constexpr int NVT = ST::N * (int)sizeof(T) / 16;
-    for (int x = tid; x < 2 * NVT; x += NT) {
-      const int t = x < NVT ? tri_incl(i, i) : tiles_p(NBK) + tiles_a(NBK) + i;
-      reinterpret_cast<u32x4_t*>(smem + lay.C)[x] =
-          rc.template ld<u32x4_t>(cr.C + ctile_bytes<T>(NBK) * m, t * ST::N * (int)sizeof(T) + 16 * (x % NVT));
-    }
-    const T* so = reinterpret_cast<const T*>(a.dO) + bh0 + (size_t)((ch * L + m * W + 16 * i) * rs);
-    for (int x = tid; x < 16 * D / VEC; x += NT)
-      stage_vec<T, D, false, false>(lds(lay.dO), x, *reinterpret_cast<const u32x4_t*>(so + (x / (D / VEC)) * rs + (x % (D / VEC)) * VEC));
-    if constexpr (!SW) p.wg[0] = rc.template ld<f32x4>(cr.W + (m * NBK + i) * NT * 16, tid * 16);
-    p.v[0] = rc.template ld<quad>(cr.V + (m * NBK + i) * NT * QB, tid * QB);
-    if (tid < D / 4)
-      *reinterpret_cast<f32x4*>(smem + lay.Gam + 16 * tid) = rc.template ld<f32x4>(cr.Gam + (m * NBK + i) * D * 4, 16 * tid);
-    if (tid < 16) {
-      ldf(lay.Beta)[tid] = rc.template ld<float>(cr.Beta + (m * W + 16 * i) * 4, 4 * tid);
-      if constexpr (SW) ldf(lay.Ws)[tid] = rc.template ld<float>(cr.Beta + (L + m * W + 16 * i) * 4, 4 * tid);
-    }
-  }
-
-  // Adjoint of one block of NB tiles whose data is in LDS (after a barrier) and
-  // p (wg, v): tiles tile0 .. tile0 + NB - 1 of chunk ch.  With next >= 0
-  // (block index of the chunk nch_) the next block's data is loaded meanwhile
-  // and put into LDS before the end; the caller's barrier publishes it.
+  // Adjoint of one block whose data is in LDS (after a barrier) and p (wg, v; a
+  // tile's in tp):
+  // tiles tile0 .. tile0 + NB - 1 of chunk ch, which is the whole block in LDS
+  // (NB = NBK) or its tile `sub` (NB = 1, a block evaluated tile by tile).
+  // NEXT: the next block's data (block next_m of this chunk, or with next_m < 0
+  // the last one of chunk wait_ch) is loaded into p meanwhile; otherwise that of
+  // the tile before into tp.  wide: the chunk's bits of blocks evaluated tile by tile.
   // wait_ch >= 0: wave 0 waits for that chunk's flag and leaves it in Ctl.
-  template <int NB>
-  __device__ __forceinline__ void block(State& s, Pre& p, f32x4 (&dF)[NRT], quad (&fU)[NRT], int ch, int tile0, int wait_ch,
-                                        bool& timed_out, int nx_ch_same, int nx_m) {
-    constexpr int W = 16 * NB;   // tokens of this block (the images in LDS have W rows)
-    constexpr int NTP = tiles_p(NB), NTA = tiles_a(NB);
+  template <int NB, bool NEXT>
+  __device__ __forceinline__ void block(State& s, Pre& p, TilePre& tp, f32x4 (&dF)[NRT], quad (&fU)[NRT], int ch, int tile0, int sub,
+                                        int wait_ch, bool& timed_out, int next_m, int wide) {
+    constexpr int W = 16 * NB;   // tokens of this block (the images in LDS have 16 NBK rows)
+    constexpr int NTP = tiles_p(NB);
+    constexpr bool TILE = NB != NBK;
     fresh();
     const RecBuf rc(rec_of(ch), cr.total);
     const int t0 = ch * L + 16 * tile0;
-    T* sKt = lds(lay.Kt);
-    T* sQt = lds(lay.Qt);
-    T* sKi = lds(lay.Ki);
-    T* sU = lds(lay.U);
-    T* sdO = lds(lay.dO);
+    // a tile takes its own rows of the images, its own coupling tiles (dA over P,
+    // dP over T) and the first rows of dM and dY
+    const int r0 = TILE ? 16 * sub : 0;
+    T* sKt = lds(lay.Kt) + r0 * RT::LD;
+    T* sQt = lds(lay.Qt) + r0 * RT::LD;
+    T* sKi = lds(lay.Ki) + r0 * RT::LD;
+    T* sU = lds(lay.U) + r0 * RT::LD;
+    T* sdO = lds(lay.dO) + r0 * RT::LD;
     T* sdM = lds(lay.dM);
-    T* sR = lds(lay.R);
-    T* sC = lds(lay.C);
+    T* sR = lds(lay.R) + r0 * RT::LD;
+    T* sP = lds(lay.C) + (TILE ? tri_incl(sub, sub) * ST::N : 0);
+    T* sA = lds(lay.C) + tiles_p(NBK) * ST::N;
+    T* sT = sA + (tiles_a(NBK) + (TILE ? sub : 0)) * ST::N;
+    T* sdA = sP;
+    T* sdP = TILE ? sT : lds(lay.C) + NTP * ST::N;
     T* sdY = lds(lay.dY);
     float* sDbeta = ldf(lay.Dbeta) + w * W;
-    float* sBeta = ldf(lay.Beta);
+    float* sBeta = ldf(lay.Beta) + r0;
+    float* sWs = ldf(lay.Ws) + r0;
     float* sGam = ldf(lay.Gam);
     const auto e0 = [&](int tt) { return (t0 + 16 * tt + c) * rs + 16 * w + 4 * g; };
 
     // ---- B1: value side (value tile w; rows t = 16 tt + 4 g + i, column v = 16 w + c)
     // S' of the block for B2, loaded ahead of this step's stores (transposed operand quads)
     quad sS[NJT];
-    {
+    if constexpr (TILE) {
+      for (int vt = 0; vt < NJT; ++vt) sS[vt] = tp.S[vt];
+    } else {
       for (int vt = 0; vt < NJT; ++vt) sS[vt] = rc.template ld<quad>(cr.S + (tile0 * NJT + vt) * NT * QB, tid * QB);
     }
     quad dOq[NB], nq[NB], dzwT[NB], dvT[NB];   // dO, -dR (K = t operands); dz_w, dv as token rows
@@ -307,7 +326,7 @@ struct Adjoint {
       for (int tt = 0; tt < NB; ++tt) {
         // (two chains, added at the end: mma16 never accumulates on a mma32 result)
         f32x4 dp = zero4();
-        for (int i = tt; i < NB; ++i) dp = Qd::mma16(ST::tr(sC + tri_incl(i, tt) * ST::N, g, c), dOq[i], dp);
+        for (int i = tt; i < NB; ++i) dp = Qd::mma16(ST::tr(sP + tri_incl(i, tt) * ST::N, g, c), dOq[i], dp);
         du[tt] = zero4();
         for (int jp = 0; jp < NJT / 2; ++jp)
           du[tt] = Qd::mma32(Qd::ld(sKi + RT::at(16 * tt + c, 32 * jp, 4 * g)), Qd::ld(sKi + RT::at(16 * tt + c, 32 * jp + 16, 4 * g)),
@@ -318,8 +337,8 @@ struct Adjoint {
       quad xq[NB];
       for (int i = NB - 1; i >= 0; --i) {
         f32x4 r = du[i];
-        for (int j = i + 1; j < NB; ++j) r = Qd::mma16(ST::tr(sC + (NTP + tri_strict(j, i)) * ST::N, g, c), xq[j], r);
-        dR[i] = ST::apply_T(ST::tr(sC + (NTP + NTA + i) * ST::N, g, c), r);
+        for (int j = i + 1; j < NB; ++j) r = Qd::mma16(ST::tr(sA + tri_strict(j, i) * ST::N, g, c), xq[j], r);
+        dR[i] = ST::apply_T(ST::tr(sT + i * ST::N, g, c), r);
         xq[i] = Qd::cvt(dR[i]);
         nq[i] = Qd::cvt(-dR[i]);
         // exchange: token rows of -dR for the products over the value axis
@@ -329,9 +348,9 @@ struct Adjoint {
       for (int tt = 0; tt < NB; ++tt) {
         const f32x4 bt = *reinterpret_cast<const f32x4*>(sBeta + 16 * tt + 4 * g);
         f32x4 wg;
-        if constexpr (SW) wg = *reinterpret_cast<const f32x4*>(ldf(lay.Ws) + 16 * tt + 4 * g);
-        else wg = p.wg[tt];
-        const f32x4 vv = Qd::f32(p.v[tt]);
+        if constexpr (SW) wg = *reinterpret_cast<const f32x4*>(sWs + 16 * tt + 4 * g);
+        else wg = TILE ? tp.wg : p.wg[tt];
+        const f32x4 vv = Qd::f32(TILE ? tp.v : p.v[tt]);
         f32x4 dvv, dzw, pr;
         for (int i = 0; i < 4; ++i) {
           const float dwv = bt[i] * dR[tt][i];
@@ -376,7 +395,10 @@ struct Adjoint {
     // E and the erase gate for the next step
     f32x4 E[NB];
     quad sig[NB];
-    for (int tt = 0; tt < NB; ++tt) {
+    if constexpr (TILE) {
+      E[0] = tp.E;
+      sig[0] = tp.sig;
+    } else for (int tt = 0; tt < NB; ++tt) {
       E[tt] = rc.template ld<f32x4>(cr.E + (tile0 + tt) * NT * 16, tid * 16);
       sig[tt] = rc.template ld<quad>(cr.Sig + (tile0 + tt) * NT * QB, tid * QB);
     }
@@ -398,8 +420,8 @@ struct Adjoint {
         accA[e] = (i > j || 4 * g + e < c) ? accA[e] : 0.0f;
         accP[e] = (i > j || 4 * g + e <= c) ? accP[e] : 0.0f;
       }
-      Qd::st(sC + x * ST::N + ST::at(c, 4 * g), Qd::cvt(accA));
-      Qd::st(sC + (NTP + x) * ST::N + ST::at(c, 4 * g), Qd::cvt(accP));
+      Qd::st(sdA + x * ST::N + ST::at(c, 4 * g), Qd::cvt(accA));
+      Qd::st(sdP + x * ST::N + ST::at(c, 4 * g), Qd::cvt(accP));
     }
     f32x4 y[NB], dQ[NB], dKi[NB];
     float dgs = 0.0f;   // sum_v dM[v][j] S'[v][j] for j = 16 w + c
@@ -439,32 +461,34 @@ struct Adjoint {
       if constexpr (!SW) Qd::st(sdM + RT::at(16 * tt + c, 16 * w, 4 * g), dzwT[tt]);
     }
     if (wait_ch >= 0) after_wait(s, timed_out);
-    const int nctl = reinterpret_cast<const int*>(smem + lay.Ctl)[0];   // wide bits of the awaited chunk, or -1
-    // the next block, if it can be prefetched: (ch, nx_m) or, at the chunk's
-    // last block, the last block of chunk ch - 1
-    int nch_ = -1, nm_ = nx_m;
-    if (nx_ch_same) nch_ = ch;
-    else if (wait_ch >= 0) {
-      nch_ = wait_ch;
-      nm_ = mpc - 1;
-      if (nctl >= 0 && ((nctl >> nm_) & 1)) nch_ = -1;
-    }
-    // (a block that is not prefetched: its caller loads it; this one's data is
+    // the next block (at the call's first block there is none: this one's data is
     // read again then, so that p is written on every path)
-    const int pch = nch_ >= 0 ? nch_ : ch, pm = nch_ >= 0 ? nm_ : tile0 / NBK;
+    int pch = ch, pm = next_m, pwide = 0;
+    if constexpr (NEXT) {
+      const int nctl = reinterpret_cast<const int*>(smem + lay.Ctl)[0];   // wide bits of the awaited chunk, or -1
+      if (next_m >= 0) {
+        pwide = (wide >> next_m) & 1;
+      } else if (wait_ch >= 0) {
+        pch = wait_ch;
+        pm = mpc - 1;
+        pwide = nctl > 0 ? (nctl >> pm) & 1 : 0;
+      } else {
+        pm = 0;
+      }
+    }
     // operands of B4 and B5, loaded ahead of this step's stores (a wait for a
     // load also waits for every store issued before it)
     quad qT[NB];
     for (int tt = 0; tt < NB; ++tt)
-      qT[tt] = rc.template ld<quad>(cr.Q + (tile0 + tt) * NT * QB, tid * QB);
+      qT[tt] = TILE ? tp.q : rc.template ld<quad>(cr.Q + (tile0 + tt) * NT * QB, tid * QB);
     quad tauq[NVS][(NB + NTW - 1) / NTW], fV[NVS][NJT];
     for (int k = 0; k < NVS; ++k)
       for (int jt = 0; jt < NJT; ++jt) fV[k][jt] = Qd::ld(opnd + ((size_t)(k * NJT + jt) * NT + tid) * 4);
     for (int k = 0; k < NVS; ++k)
       for (int u = 0; u < (NB + NTW - 1) / NTW; ++u) {
-        const int rt = w % NRW + k * NRW, tt = w / NRW + u * NTW;
-        if (tt < NB)
-          tauq[k][u] = rc.template ld<quad>(cr.Tau + (16 * (tile0 + tt) * RF + 16 * rt) * (int)sizeof(T), (c * RF + 4 * g) * (int)sizeof(T));
+        const int tt = w / NRW + u * NTW;
+        if constexpr (TILE) tauq[k][u] = tp.tau[k];
+        else if (tt < NB) tauq[k][u] = load_tau(rc, tile0 + tt, w % NRW + k * NRW);
       }
     f32x4 km[NB];
     f32x4 dgg;
@@ -485,8 +509,8 @@ struct Adjoint {
       }
       for (int i = 0; i < NB; ++i)
         for (int j = 0; j <= i; ++j) {
-          const T* ta = sC + tri_incl(i, j) * ST::N;
-          const T* tp = sC + (NTP + tri_incl(i, j)) * ST::N;
+          const T* ta = sdA + tri_incl(i, j) * ST::N;
+          const T* tp = sdP + tri_incl(i, j) * ST::N;
           y[i] = Qd::mma16(kiT[j], Qd::ld(ta + ST::at(c, 4 * g)), y[i]);
           dQ[i] = Qd::mma16(kiT[j], Qd::ld(tp + ST::at(c, 4 * g)), dQ[i]);
           dKi[j] = Qd::mma32(ktT[i], qtT[i], ST::tr(ta, g, c), ST::tr(tp, g, c), dKi[j]);
@@ -551,8 +575,11 @@ struct Adjoint {
     fresh();
     // operands of B5 and of the glue, ahead of the next block's data
     quad FT[NRT];
-    for (int rt = 0; rt < NRT; ++rt) fU[rt] = Qd::ld(opnd + ((size_t)(NVS * NJT + rt) * NT + tid) * 4);
-    for (int rt = 0; rt < NRT; ++rt) FT[rt] = rc.template ld<quad>(cr.FT + rt * NT * QB, tid * QB);
+    if constexpr (TILE) {
+      for (int rt = 0; rt < NRT; ++rt) FT[rt] = tp.FT[rt];
+    } else {
+      load_fold(fU, FT, ch);
+    }
     for (int k = 0; k < NVS; ++k)
       for (int u = 0; u < (NB + NTW - 1) / NTW; ++u) {
         const int rt = w % NRW + k * NRW, tt = w / NRW + u * NTW;
@@ -571,11 +598,13 @@ struct Adjoint {
     store_rows<NB>(a.dk, sU, t0);
     store_rows<NB>(a.dbx, sR, t0);
     if constexpr (!SW) store_rows<NB>(a.dwx, sdM, t0);
-    // the next block's data, on its way during B5 and the glue
-    if constexpr (NB == NBK) {
+    // the next block's (tile's) data, on its way during B5 and the glue
+    if constexpr (NEXT) {
       load_tiles(p, pch, pm);
-      load_scalars(p, pch, pm);
+      load_scalars(p, pch, pm, pwide);
       load_uo(p, pch, pm);
+    } else {
+      load_tile(tp, ch, tile0 - 1);
     }
     // dbeta (and the scalar write gate's dwx): the waves' partials in order
     if (w == NW - 1)
@@ -593,15 +622,18 @@ struct Adjoint {
     // ---- B5: dF += dY^T q, dq = dQt E + dY F (key tile w) ------------------------------
     fresh();
     // dF starts from that of the chunk's later blocks, parked in its record
-    for (int rt = 0; rt < NRT; ++rt) dF[rt] = zero4();
-    if (16 * (tile0 + NB) < L) {
+    // (a block's tiles hand it on in registers)
+    if (!TILE || sub == NBK - 1)
+      for (int rt = 0; rt < NRT; ++rt) dF[rt] = zero4();
+    if (16 * (tile0 + NB) < L && (!TILE || sub == NBK - 1)) {
       const float* dFr = reinterpret_cast<const float*>(rec_of(ch) + cr.dF) + (size_t)(16 * w + c) * RF + 4 * g;
       for (int rt = 0; rt < NRT; ++rt) dF[rt] = *reinterpret_cast<const f32x4*>(dFr + 16 * rt);
       // (waited for here: a load still pending where the two paths join would
       // make both of them wait, for the next block's data too)
       for (int rt = 0; rt < NRT; ++rt) arrived(dF[rt]);
     }
-    for (int rt = 0; rt < NRT; ++rt) arrived(fU[rt]);
+    if constexpr (!TILE)
+      for (int rt = 0; rt < NRT; ++rt) arrived(fU[rt]);
     for (int rt = 0; rt < NRT; ++rt) {
       if constexpr (NB == 1) {
         dF[rt] = Qd::mma16(RY::tr(sdY, 0, 16 * rt, g, c), qT[0], dF[rt]);
@@ -619,7 +651,7 @@ struct Adjoint {
       Qd::st(sR + RT::at(16 * tt + c, 16 * w, 4 * g), Qd::cvt(acc));
     }
     for (int rt = 0; rt < NRT; ++rt) arrived(dF[rt]);
-    if (tile0 > 0) park_dF(dF, ch);
+    if (tile0 > 0 && (!TILE || sub == 0)) park_dF(dF, ch);
   }
   // NB * 16 token rows of a tile to the rows from t0 on of a token tensor
   template <int NB>
@@ -736,12 +768,18 @@ struct Adjoint {
       s.dS[jt] = a.dS_T ? gload4(a.dS_T + soff + (16 * w + c) * D + 16 * jt + 4 * g) : zero4();
     s.gA = s.gT = zero4();
     Pre p;
+    TilePre tp;
     bool timed_out = false;
-    int dq_t0 = -1;         // first token of the block whose dq rows are in LDS
-    bool in_regs = false;   // the next block's data is (on its way) in p
+    int dq_t0 = -1;   // first token of the block whose dq rows are in LDS
     if (w == 0) wait_ready(nch - 1, false);
     __syncthreads();
     after_wait(s, timed_out);
+    {
+      const int ctl = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(smem + lay.Ctl)[0]);
+      load_tiles(p, nch - 1, mpc - 1);
+      load_scalars(p, nch - 1, mpc - 1, ctl > 0 && ((ctl >> (mpc - 1)) & 1));
+      load_uo(p, nch - 1, mpc - 1);
+    }
 
 #pragma unroll 1
     for (int ch = nch - 1; ch >= 0; --ch) {
@@ -753,47 +791,34 @@ struct Adjoint {
 #pragma unroll 1
       for (int m = mpc - 1; m >= 0; --m) {
         const int wait_ch = m == 0 ? ch - 1 : -1;
-        if (!((wide >> m) & 1)) {
-          if (!in_regs) {
-            load_tiles(p, ch, m);
-            load_scalars(p, ch, m);
-            load_uo(p, ch, m);
-          }
-          load_vals(p, ch, m);   // (first used in the middle of B1)
-          // (the last readers of the other regions were before B5; U and dO are
-          // read by the glue)
-          put_tiles(p);
-          __syncthreads();
-          if (dq_t0 >= 0) store_rows<NBK>(a.dq, lds(lay.R), dq_t0);
-          put_uo(p);
-          __syncthreads();
-          const bool same = m > 0 && !((wide >> (m - 1)) & 1);
-          block<NBK>(s, p, dF, fU, ch, m * NBK, wait_ch, timed_out, same ? 1 : 0, m - 1);
-          dq_t0 = ch * L + m * W;
-          in_regs = same;
-          if (m == 0 && ch > 0) {
-            const int nc = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int*>(smem + lay.Ctl)[0]);
-            in_regs = !(nc > 0 && ((nc >> (mpc - 1)) & 1));
-          }
-          if (m == 0) glue(s, dF, fU, ch);
+        load_vals(p, ch, m);   // (first used in the middle of B1)
+        // (the last readers of the other regions were before B5; U and dO are
+        // read by the glue)
+        put_tiles(p);
+        __syncthreads();
+        if (dq_t0 >= 0) store_rows<NBK>(a.dq, lds(lay.R), dq_t0);
+        put_uo(p);
+        __syncthreads();
+        if (NBK == 1 || !((wide >> m) & 1)) {
+          block<NBK, true>(s, p, tp, dF, fU, ch, m * NBK, 0, wait_ch, timed_out, m - 1, wide);
         } else if constexpr (NBK > 1) {
+          // tile by tile, from the same data in LDS; a tile's reference, gates and
+          // values are loaded during the one after it
+          load_tile(tp, ch, m * NBK + NBK - 1);
+          load_fold(fU, tp.FT, ch);
 #pragma unroll 1
-          for (int i = NBK - 1; i >= 0; --i) {
+          for (int i = NBK - 1; i > 0; --i) {
+            block<1, false>(s, p, tp, dF, fU, ch, m * NBK + i, i, -1, timed_out, -1, 0);
+            put_gam(tp.gam);   // (last read in B1)
             __syncthreads();
-            if (dq_t0 >= 0) store_rows<NBK>(a.dq, lds(lay.R), dq_t0);
-            dq_t0 = -1;
-            load_tile_direct(p, ch, m, i);
-            __syncthreads();
-            block<1>(s, p, dF, fU, ch, m * NBK + i, i == 0 ? wait_ch : -1, timed_out, 0, 0);
-            __syncthreads();
-            store_rows<1>(a.dq, lds(lay.R), ch * L + m * W + 16 * i);
           }
+          block<1, true>(s, p, tp, dF, fU, ch, m * NBK, 0, wait_ch, timed_out, m - 1, wide);
           // nothing of this path is pending where it joins the other one (the
-          // join would wait for the next block's data otherwise)
+          // join would make that one wait for the next block's data otherwise)
           vm_wait_all();
-          in_regs = false;
-          if (m == 0) glue(s, dF, fU, ch);
         }
+        dq_t0 = ch * L + m * W;
+        if (m == 0) glue(s, dF, fU, ch);
       }
     }
     __syncthreads();
