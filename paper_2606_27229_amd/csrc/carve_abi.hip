@@ -29,7 +29,8 @@ int pick_nb(const carve_dims_t* d) {
 
 // backward workspace: d[Ub; Uw] partials per (b,h, chunk split) | dVb, dVw
 // partials per (b,h, token split) | chunk records of the recompute | ready
-// flags and ticket counter of the fused recompute + adjoint launch
+// flags, ticket counter and adjoint positions of the fused recompute + adjoint
+// launch | dA, dtau partials | the adjoints' parameter operands
 struct BwdWs {
   size_t part, partV, rec, sync, partG, opnd, total;
 };
@@ -39,8 +40,9 @@ BwdWs bwd_workspace_layout(const carve_dims_t* d) {
   const size_t nbh = (size_t)d->B * d->H;
   const size_t nch = (size_t)(d->T / d->L);
   size_t off = 0;
-  l.part = off;  off += align256(nbh * kMaxParamSplits * part_floats(d->R, d->Dk) * 4);
-  l.partV = off; off += align256(nbh * kMaxParamSplits * part_floats(d->R, d->Dk) * 4);
+  const size_t npart = nbh * param_splits(d->B * d->H);
+  l.part = off;  off += align256(npart * part_floats(d->R, d->Dk) * 4);
+  l.partV = off; off += align256(npart * part_floats(d->R, d->Dk) * 4);
   // records of the full layer (2RP fold rows); the scalar-write records are smaller
   l.rec = off;   off += align256(nbh * nch * chunk_rec_bytes(d->dtype, d->Dk, d->L, 2 * round_rp(d->R), pick_nb(d)));
   l.sync = off;  off += align256(sync_ints(nbh, nch) * sizeof(int));

@@ -225,6 +225,22 @@ def test_backward_workspace_holds_the_chunk_records(D, R, L, dt):
     assert lib.carve_workspace_size(ctypes.byref(d), 1) >= B * H * (T // L) * per
 
 
+@pytest.mark.parametrize("B,H", [(1, 1), (2, 16), (4, 16), (32, 16), (64, 64)])
+def test_backward_workspace_holds_no_more_partials_than_are_written(B, H):
+    """The parameter-gradient partials are two kinds of records of 2 R D floats,
+    16 of each per (batch, head) or as many as make 512 of a kind, and at least one; a
+    second chunk adds one record per (batch, head) and its ready flag."""
+    lib = carve.load_library()
+    D, R, L, n = 128, 32, 64, B * H
+    size = [lib.carve_workspace_size(ctypes.byref(carve.Dims(B, T, H, D, D, R, L, carve.CARVE_BF16)), 1)
+            for T in (L, 2 * L)]
+    rest = size[0] - (size[1] - size[0])
+    parts = 2 * n * max(1, min(16, -(-512 // n))) * 2 * R * D * 4
+    # each adjoint's operand quads of V and [Ub; Uw], its gate constants, dA and dtau
+    operands = n * ((D // 16 + 2 * R // 16) * D * 4 * 8 + 2 * D * 4 * 16 + 2 * D * 4)
+    assert parts <= rest <= parts + operands + 16 * n + 8192
+
+
 def test_rmsnorm_validation():
     lib = carve.load_library()
     fake = ctypes.c_void_p(4096)
