@@ -278,11 +278,11 @@ int carve_rmsnorm_bwd_noalloc(const carve_dims_t* d, const void* o, const float*
 /* Measurement hook (not part of the computation).  Arms the next
  * carve_chunk_* or carve_rmsnorm_* call made on the calling thread to record
  * events[0] on its stream before its first kernel launch and events[i] after
- * its i-th launch (the forward makes 1 launch; the backward 6: clear of the
- * chunk ready flags, chunk recompute fused with the adjoint, dVb/dVw
- * partials, d[Ub;Uw] partials, two fixed-order reductions; the gated backward
- * a 7th, the reduction of dA, dtau over the batch; the backward with the
- * input activations a 7th, the activation gradient of dq, dk; the norm's
+ * its i-th launch (the forward makes 1 launch; the backward 4: clear of the
+ * chunk ready flags, chunk recompute fused with the adjoint, the partials of
+ * d[Ub;Uw] and dVb/dVw, their fixed-order reductions; the gated backward
+ * a 5th, the reduction of dA, dtau over the batch; the backward with the
+ * input activations a 5th, the activation gradient of dq, dk; the norm's
  * forward 1, its backward 2),
  * up to `capacity` events.  `events` are hipEvent_t handles created by the
  * caller (hipEventCreate) and owned by the caller; the handles are copied
@@ -298,7 +298,8 @@ int carve_profile_events(hipEvent_t* events, int capacity);
  * for the records of the next chunks with a bounded poll of their ready flags
  * (by default 2^20 polls, about a second; a correct launch never reaches it,
  * since a chunk is recomputed in tens of microseconds by a workgroup that is
- * already running).  If the bound runs out, the wave fills its state gradient
+ * already running and whose own wait is shorter and made once).  If the bound
+ * runs out, the wave fills its state gradient
  * with NaN, so the gradients of all earlier tokens come out NaN, waits no
  * more, and sets a timeout word in the workspace's synchronisation area.  The
  * call itself still returns CARVE_OK, as kernel completion is asynchronous.

@@ -1,6 +1,7 @@
 // carve_bwd.hip -- the parameter-gradient kernels of the CARVE backward
-// (steps 3-6 of the launch sequence in carve_bwd.h), the synchronisation-area
-// clear, and the variant dispatch of the fused recompute + adjoint launch.
+// (steps 3 and 4 of the launch sequence in carve_bwd.h), the synchronisation-area
+// clear (step 1), the reductions and the activation gradient that follow in some
+// variants, and the variant dispatch of the fused recompute + adjoint launch.
 #include "carve_param.h"
 
 namespace carve {
