@@ -310,8 +310,7 @@ int bwd_impl(const carve_dims_t* d, const void* q, const void* k, const void* v,
   f.rec = wsb + wl.rec;
   f.B = d->B; f.T = d->T; f.H = d->H; f.R = d->R; f.RP = RP; f.L = d->L;
   BwdArgs a;
-  a.q = q; a.k = k; a.v = v; a.beta = beta; a.bx = bx; a.wx = wx;
-  a.g = dc.g; a.Ub = Ub; a.Uw = Uw; a.Vb = Vb; a.Vw = Vw; a.S_chunks = S_chunks;
+  a.v = v; a.Ub = Ub; a.Uw = Uw; a.Vb = Vb; a.Vw = Vw; a.S_chunks = S_chunks;
   a.f = dc.f; a.A = dc.A; a.tau_f = dc.tau_f;
   a.dO = dO; a.dS_T = dS_T;
   a.dq = dq; a.dk = dk; a.dv = dv; a.dbeta = dbeta; a.dbx = dbx; a.dwx = dwx; a.dg = dd.dg; a.dS0 = dS0;

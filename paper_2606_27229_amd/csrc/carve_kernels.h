@@ -329,12 +329,12 @@ size_t chain_lds_bytes(int dtype, int D, int WB, int RP);
 
 // ---- backward -----------------------------------------------------------------
 struct BwdArgs {
-  const void *q, *k, *v, *beta, *bx, *wx;   // wx (and dwx) [B,T,H] with the scalar write gate
-  const float *g, *Ub, *Uw, *Vb, *Vw;
+  const void* v;    // the raw values (activated inputs); the rest comes from the records
+  const float *Ub, *Uw, *Vb, *Vw;
   const float* S_chunks;
   const void* dO;
   const float* dS_T;
-  void *dq, *dk, *dv, *dbeta, *dbx, *dwx;
+  void *dq, *dk, *dv, *dbeta, *dbx, *dwx;   // dwx [B,T,H] with the scalar write gate
   float* dg;
   // gated kernels: decay logit and its parameters, df (token dtype) instead of
   // dg, per-(b,h) partial dA, dtau ([B*H][2][Dk] f32, workspace)
