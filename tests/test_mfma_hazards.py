@@ -8,7 +8,7 @@ product's result may be read after 8 wait states, which is what the compiler
 leaves before every other reader.  So no such pair may lie closer than that in
 the library, along any path of the code, branches included.
 
-The checker follows the disassembly of the library built from this repository.
+The scan follows the disassembly of the library built from this repository.
 """
 import os
 import re
@@ -102,7 +102,7 @@ K16 = ("v_mfma_f32_16x16x16_bf16 v[0:3], v[8:9], v[12:13], v[4:7]", None)
 END = ("s_endpgm", None)
 
 
-def test_checker_on_short_listings():
+def test_scan_on_short_listings():
     assert close_pairs(_text(K32, K16, END))
     assert close_pairs(_text(K32, ("s_nop 6", None), K16, END))
     assert not close_pairs(_text(K32, ("s_nop 7", None), K16, END))
